@@ -82,22 +82,14 @@ struct ConvArgs {
     // output channel (co > ci here): the input gradient's weights of a
     // masked convolution with kernel M.
     int flip, fself;
-    // trows (R = 1 launches; 0 = off): Wt is a 3 x 3 kernel M (trows, K, 3, 3)
-    // read with the taps as rows, W[t trows + c][k] = M[c][k][t]: the GEMM
-    // whose nine row blocks, shifted and added, give M's convolution
-    int trows;
 };
 
 constexpr int kConvThreads = 256;
-constexpr long long kWideSmallGrid = 256;   // blocks: one per compute unit
 constexpr int kSK = 68;     // LDS row stride (floats) of 64-value k chunks
 
-// k values staged at a time (KC): by default 32 for the 64 c_out x 64 px
-// tile (half the LDS of 64, so twice the blocks a compute unit holds: 4-19%
-// faster on the flow's 1 x 1 GEMMs when the grid covers the chip), 64 for
-// the narrow tiles (a block's 16 weight rows are staged by 256 threads a
-// quad each).  Grids of fewer blocks than compute units take 64: there the
-// chunk loop's length, not occupancy, sets the time.
+// k values staged at a time (KC): 32 for the 64 c_out x 64 px tile (half the
+// LDS of 64, so twice the blocks a compute unit holds), 64 for the narrow
+// tiles (a block's 16 weight rows are staged by 256 threads a quad each).
 template <int WCO>
 constexpr int conv_kc() {
     return WCO == 4 ? 32 : 64;
@@ -150,24 +142,17 @@ __device__ __forceinline__ void conv_tile(const ConvArgs &a, int bx, int by, int
             const int col = idx / KQ, kk = k0 + 4 * (idx % KQ);
             const int co = co0 + col;
             const float *w = a.Wt + (long long)(co < a.Co ? co : 0) * a.K;
-            long long trow = 0;   // (trows) M's row c and tap t of row co
-            int ttap = 0;
-            if (a.trows) {
-                const int cc = co < a.Co ? co : 0;
-                ttap = cc / a.trows;
-                trow = (long long)(cc - ttap * a.trows) * a.K;
-            }
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 bool ok = co < a.Co && kk + e < a.K;
-                long long off = a.trows ? (trow + kk + e) * 9 + ttap : kk + e;
+                long long off = kk + e;
                 if (a.flip) {   // M[ci][co][R^2 - 1 - t], t = a R + c
                     const int ci = (int)((unsigned)(kk + e) / (R * R));
                     const int t = R * R - 1 - (kk + e - ci * R * R);
                     off = ((long long)ci * a.Co + co) * (R * R) + t;
                     ok = ok && !(t == a.fself && co > ci);
                 }
-                const float v = (a.flip || a.trows ? a.Wt : w)[ok ? off : 0];
+                const float v = (a.flip ? a.Wt : w)[ok ? off : 0];
                 ra[u][e] = ok ? v : 0.0f;
             }
         }
@@ -282,15 +267,6 @@ __global__ __launch_bounds__(kConvThreads) void conv_kernel(ConvArgs a) {
     conv_tile<R, WCO, NS, KC>(a, blockIdx.x, blockIdx.y, blockIdx.z, lds);
 }
 
-// The 64 x 64 tile's launch, its chunk chosen by the grid's size.
-template <int R>
-void launch_wide(const ConvArgs &a, dim3 grid, hipStream_t st) {
-    if ((long long)grid.x * grid.y * grid.z < kWideSmallGrid)
-        hipLaunchKernelGGL((conv_kernel<R, 4, 4, 64>), grid, dim3(kConvThreads), 0, st, a);
-    else
-        hipLaunchKernelGGL((conv_kernel<R, 4, 4, 32>), grid, dim3(kConvThreads), 0, st, a);
-}
-
 // The parts of a K-split convolution added in order (part 0 first), then
 // bias, ReLU and the output scale, as the unsplit kernel's epilogue does.
 __global__ __launch_bounds__(256) void conv_reduce_kernel(ConvArgs a, int parts) {
@@ -317,15 +293,9 @@ int conv_launched() { return hipGetLastError() == hipSuccess ? FINC_OK : FINC_EH
 // take kMaxParts Co B H W floats).
 constexpr int kMaxParts = 8;
 
-// Launch of one convolution with kernel size R (a compile-time instance).
-// ph, pw < 0 mean "same" padding, (R - 1) / 2.  Narrow outputs (C_out < 64)
-// with a long K are split into parts of at least 8 chunks, so that the grid
-// covers the chip: the number of parts depends on K only (not on the batch)
-// and the parts are added in order, so results stay deterministic and
-// independent of B.  partial: kMaxParts Co B H W floats, or null (no split).
-// The shifted sum of the nine row blocks of a tap-rows GEMM Z (B, 9 C, H, W):
-// y[b][c][i][j] = (bias[c] + sum over taps t = 3 a + d, in order, of
-// Z[b][t C + c][i + a - 1][j + d - 1], zero outside) * exp(3 ls[c]).
+// The shifted sum of the nine tap rows of each channel of a tap-rows GEMM
+// Z (B, 9 C, H, W): y[b][c][i][j] = (bias[c] + sum over taps t = 3 a + d, in
+// order, of Z[b][9 c + t][i + a - 1][j + d - 1], zero outside) * exp(3 ls[c]).
 __global__ __launch_bounds__(256) void shift_add_kernel(const float *Z, float *y, long long ys,
                                                         const float *bias, const float *ls,
                                                         int B, int C, int H, int W, Div d_HW,
@@ -341,7 +311,7 @@ __global__ __launch_bounds__(256) void shift_add_kernel(const float *Z, float *y
         for (int t = 0; t < 9; ++t) {
             const int ii = i + t / 3 - 1, jj = j + t % 3 - 1;
             if (ii >= 0 && ii < H && jj >= 0 && jj < W)
-                v += zb[(long long)(t * C + c) * HW + ii * W + jj];
+                v += zb[(long long)(9 * c + t) * HW + ii * W + jj];
         }
         v += bias ? bias[c] : 0.0f;
         if (ls)
@@ -350,12 +320,10 @@ __global__ __launch_bounds__(256) void shift_add_kernel(const float *Z, float *y
     }
 }
 
-template <int R>
-int launch_conv_r(const float *x, long long xs, float *y, long long ys, const float *Wt,
-                  const float *bias, const float *ls, int relu, int B, int Ci, int Co, int H, int W,
-                  int ph, int pw, hipStream_t st, float *partial) {
-    if (B == 0)
-        return FINC_OK;
+// Arguments of an R x R "same" convolution.
+inline ConvArgs conv_args(const float *x, long long xs, float *y, long long ys, const float *Wt,
+                          const float *bias, const float *ls, int relu, int B, int Ci, int Co,
+                          int H, int W, int R) {
     ConvArgs a;
     memset(&a, 0, sizeof(a));
     a.x = x;
@@ -370,18 +338,22 @@ int launch_conv_r(const float *x, long long xs, float *y, long long ys, const fl
     a.H = H;
     a.W = W;
     a.K = Ci * R * R;
-    a.ph = ph < 0 ? (R - 1) / 2 : ph;
-    a.pw = pw < 0 ? (R - 1) / 2 : pw;
+    a.ph = a.pw = (R - 1) / 2;
     a.xs = xs;
     a.ys = ys;
     a.d_HW = make_div(H * W);
     a.d_W = make_div(W);
-    const long long Q = (long long)B * H * W;
-    if (Co >= 64) {
-        const dim3 grid(cdiv(Q, 64), cdiv(Co, 64));
-        launch_wide<R>(a, grid, st);
-        return conv_launched();
-    }
+    return a;
+}
+
+// A narrow R x R "same" convolution (C_out < 64, compile-time instances of
+// R).  A long K is split into parts of at least 8 chunks, so that the grid
+// covers the chip: the number of parts depends on K only (not on the batch)
+// and the parts are added in order, so results stay deterministic and
+// independent of B.  partial: kMaxParts Co B H W floats, or null (no split).
+template <int R>
+int launch_conv_r(ConvArgs a, hipStream_t st, float *partial) {
+    const long long Q = (long long)a.B * a.H * a.W;
     const int nchunk = cdiv(a.K, conv_kc<1>());
     int parts = 1;
     if (partial)
@@ -390,13 +362,13 @@ int launch_conv_r(const float *x, long long xs, float *y, long long ys, const fl
     a.cps = cdiv(nchunk, parts);
     parts = cdiv(nchunk, a.cps);
     a.partial = parts > 1 ? partial : nullptr;
-    const dim3 grid(cdiv(Q, 128), cdiv(Co, 16), parts);
+    const dim3 grid(cdiv(Q, 128), cdiv(a.Co, 16), parts);
     hipLaunchKernelGGL((conv_kernel<R, 1, 2>), grid, dim3(kConvThreads), 0, st, a);
     if (parts > 1) {
         const int rc = conv_launched();
         if (rc != FINC_OK)
             return rc;
-        const long long n = (long long)Co * Q;
+        const long long n = (long long)a.Co * Q;
         hipLaunchKernelGGL(conv_reduce_kernel, dim3((unsigned)(n / 256 + 1 < 8192 ? n / 256 + 1 : 8192)),
                            dim3(256), 0, st, a, parts);
     }

@@ -16,14 +16,13 @@
 //    of a 3x3 conv (bias, exp(3 ls) scale) of h1; log|det| -sum logsd.
 //
 // Design:
-//  * Every convolution of the coupling and prior networks, and the 1x1
-//    convolution, is one kernel: an fp32 MFMA implicit GEMM
-//    (v_mfma_f32_16x16x4_f32), D[c_out][pixel] = sum over k = (c_in, tap) of
-//    W[c_out][k] x[k][pixel], with the K axis staged through LDS 64 values
-//    at a time (weights and the gathered input window, both k-contiguous so
-//    one 16-byte LDS read feeds four MFMAs), the next chunk's global loads
-//    in flight during the current chunk's MFMAs, and bias, ReLU and the
-//    output scale fused into the store.
+//  * The coupling network is one launch up to its last convolution's tap
+//    products (coupling_net.h), on the bf16 matrix cores at fp32 precision;
+//    beyond its widths, or with too few pixels for its scratch, one GEMM a
+//    layer (split_gemm.h).  The narrow convolutions (the prior's, the 1x1) are
+//    fp32 MFMA implicit GEMMs (conv_gemm.h), D[c_out][pixel] = sum over
+//    k = (c_in, tap) of W[c_out][k] x[k][pixel], the K axis staged through LDS,
+//    bias, ReLU and the output scale fused into the store.
 //  * The 1x1 convolution and the actnorm next to it are one affine map per
 //    pixel: prepared once per weight set in fp64 (Wm diag(s), Wm b forward;
 //    diag(1/s) Wm^-1, -b/s inverse, by Gauss-Jordan elimination with partial
@@ -41,7 +40,9 @@
 #include <string.h>
 
 #include "conv_gemm.h"
+#include "coupling_net.h"
 #include "finc.h"
+#include "split_gemm.h"
 
 namespace {
 
@@ -308,15 +309,30 @@ inline bool overlap(const void *a, size_t na, const void *b, size_t nb) {
 int launched() { return hipGetLastError() == hipSuccess ? FINC_OK : FINC_EHIP; }
 
 // The flow's convolutions: 3 x 3 "same" (coupling and prior networks) and
-// 1 x 1 (the coupling's middle convolution, the 1x1 / actnorm map).
+// 1 x 1 (the coupling's middle convolution, the 1x1 / actnorm map), from 64
+// output channels on (split: always) on the bf16 matrix cores.
 int launch_conv(const float *x, long long xs, float *y, long long ys, const float *Wt,
                 const float *bias, const float *ls, int relu, int B, int Ci, int Co, int H, int W,
-                int R, hipStream_t st, float *partial = nullptr) {
+                int R, hipStream_t st, float *partial = nullptr, bool split = false) {
+    if (B == 0)
+        return FINC_OK;
+    const ConvArgs a = conv_args(x, xs, y, ys, Wt, bias, ls, relu, B, Ci, Co, H, W, R);
+    if (Co < 64 && !split)
+        return R == 1 ? launch_conv_r<1>(a, st, partial) : launch_conv_r<3>(a, st, partial);
     if (R == 1)
-        return launch_conv_r<1>(x, xs, y, ys, Wt, bias, ls, relu, B, Ci, Co, H, W, -1, -1, st,
-                                partial);
-    return launch_conv_r<3>(x, xs, y, ys, Wt, bias, ls, relu, B, Ci, Co, H, W, -1, -1, st,
-                            partial);
+        launch_split<1, false>(a, st);
+    else
+        launch_split<3, false>(a, st);
+    return launched();
+}
+
+int launch_shift_add(const float *Z, float *y, long long ys, const float *bias, const float *ls,
+                     int B, int C, int H, int W, hipStream_t st) {
+    const long long n = (long long)B * C * H * W;
+    hipLaunchKernelGGL(shift_add_kernel, dim3((unsigned)(n / 256 + 1 < 8192 ? n / 256 + 1 : 8192)),
+                       dim3(256), 0, st, Z, y, ys, bias, ls, B, C, H, W, make_div(H * W),
+                       make_div(W), make_div(C));
+    return launched();
 }
 
 // A 3 x 3 "same" convolution with few output channels (9 C >= 64) and a
@@ -328,33 +344,13 @@ int launch_conv_taps(const float *x, long long xs, float *y, long long ys, const
                      hipStream_t st, float *Z) {
     if (B == 0)
         return FINC_OK;
-    ConvArgs a;
-    memset(&a, 0, sizeof(a));
-    a.x = x;
-    a.y = Z;
-    a.Wt = Wt;
-    a.B = B;
-    a.Ci = Ci;
-    a.Co = 9 * C;
-    a.H = H;
-    a.W = W;
-    a.K = Ci;
-    a.xs = xs;
-    a.ys = (long long)9 * C * H * W;
-    a.d_HW = make_div(H * W);
-    a.d_W = make_div(W);
-    a.trows = C;
-    const long long Q = (long long)B * H * W;
-    const dim3 grid(cdiv(Q, 64), cdiv(9 * C, 64));
-    launch_wide<1>(a, grid, st);
+    const ConvArgs a =
+        conv_args(x, xs, Z, 9ll * C * H * W, Wt, nullptr, nullptr, 0, B, Ci, 9 * C, H, W, 1);
+    launch_split<1, true>(a, st);
     int rc = launched();
     if (rc != FINC_OK)
         return rc;
-    const long long n = (long long)B * C * H * W;
-    hipLaunchKernelGGL(shift_add_kernel, dim3((unsigned)(n / 256 + 1 < 8192 ? n / 256 + 1 : 8192)),
-                       dim3(256), 0, st, Z, y, ys, bias, ls, B, C, H, W, make_div(H * W),
-                       make_div(W), make_div(C));
-    return launched();
+    return launch_shift_add(Z, y, ys, bias, ls, B, C, H, W, st);
 }
 
 // Offsets (floats) of one Step's parameters.
@@ -466,18 +462,106 @@ StepScratch carve(void *ws, int B, int C, int H, int W, int hid) {
     return s;
 }
 
-// The coupling network on the first half of v (image stride vs) -> hh.
+// The coupling network in one launch (coupling_net_kernel): its shape, and the
+// weights of several Steps packed for it into t1 and t2 (neighbours), which
+// it does not use otherwise.
+struct NetShape {
+    int n1, nh, nz;
+    long long floats;   // packed, one Step
+};
+NetShape net_shape(const StepLayout &L) {
+    NetShape n;
+    n.n1 = cdiv(9 * L.Ch, 32);
+    n.nh = cdiv(L.hid, 32);
+    n.nz = cdiv(9 * L.C, 32);
+    n.floats = net_pack_floats(n.n1, n.nh, n.nz);
+    return n;
+}
+
+// How many Steps' networks, at most n, the scratch holds packed; 0: hid is
+// too wide for the kernel's LDS, or not one fits (few pixels, B H W below
+// about 1,000 at hid = 512): the convolutions then run one by one.
+int net_room(const StepLayout &L, int B, int H, int W, int n) {
+    const long long room = L.hid <= kNetMaxHid ? 2ll * B * L.hid * H * W / net_shape(L).floats : 0;
+    return (int)(room < n ? room : n);
+}
+
+// The networks of the n Steps from sp on.
+int pack_nets(const float *sp, const StepLayout &L, const StepScratch &s, int n, hipStream_t st) {
+    if (n == 0)
+        return FINC_OK;
+    const NetShape ns = net_shape(L);
+    PackArgs a;
+    a.W1 = sp + L.w1;
+    a.W2 = sp + L.w2;
+    a.W3 = sp + L.w3;
+    a.ps = L.total;
+    a.os = ns.floats;
+    a.out = s.t1;
+    a.K1 = 9 * L.Ch;
+    a.C = L.C;
+    a.hid = L.hid;
+    a.n1 = ns.n1;
+    a.nh = ns.nh;
+    a.nz = ns.nz;
+    hipLaunchKernelGGL(net_pack_kernel, dim3(cdiv(ns.floats / kNetStep, 2), n), dim3(256), 0, st, a);
+    return launched();
+}
+
+// The coupling network on the first half of v (image stride vs) -> hh.  pk:
+// its packed weights, or null.
 int coupling_net(const float *v, long long vs, const float *sp, const StepLayout &L,
-                 const StepScratch &s, int B, int H, int W, hipStream_t st) {
+                 const StepScratch &s, int B, int H, int W, const float *pk, hipStream_t st) {
     const long long hw = (long long)H * W;
+    if (B == 0)
+        return FINC_OK;
+    if (pk) {
+        NetArgs a;
+        memset(&a, 0, sizeof(a));
+        a.v = v;
+        a.vs = vs;
+        a.W1 = sp + L.w1;
+        a.b1 = sp + L.b1;
+        a.W2 = sp + L.w2;
+        a.b2 = sp + L.b2;
+        a.W3 = sp + L.w3;
+        a.pk = pk;
+        a.Z = s.part;
+        a.B = B;
+        a.Ch = L.Ch;
+        a.C = L.C;
+        a.hid = L.hid;
+        a.H = H;
+        a.W = W;
+        const NetShape ns = net_shape(L);
+        a.n1 = ns.n1;
+        a.nh = ns.nh;
+        a.nz = ns.nz;
+        a.d_HW = make_div(H * W);
+        a.d_W = make_div(W);
+        const size_t lds = net_lds_bytes(a);
+        const void *k = reinterpret_cast<const void *>(coupling_net_kernel);
+        if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+            hipSuccess)
+            (void)hipGetLastError();   // not needed on every runtime; the launch check decides
+        void *args[] = {&a};
+        (void)hipLaunchKernel(k, dim3(cdiv(B * hw, kNetPx)), dim3(kNetThreads), args, lds, st);
+        const int rc = launched();
+        return rc == FINC_OK ? launch_shift_add(s.part, s.hh, (long long)L.C * hw, sp + L.b3,
+                                                sp + L.ls3, B, L.C, H, W, st)
+                             : rc;
+    }
+    // one by one; up to kNetMaxHid by the kernels that give the one launch's
+    // bits, so that results do not depend on which of the two a batch takes
+    const bool same = L.hid <= kNetMaxHid;
     int rc = launch_conv(v, vs, s.t1, (long long)L.hid * hw, sp + L.w1, sp + L.b1, nullptr, 1, B,
-                         L.Ch, L.hid, H, W, 3, st);
+                         L.Ch, L.hid, H, W, 3, st, nullptr, same);
     if (rc == FINC_OK)
         rc = launch_conv(s.t1, (long long)L.hid * hw, s.t2, (long long)L.hid * hw, sp + L.w2,
-                         sp + L.b2, nullptr, 1, B, L.hid, L.hid, H, W, 1, st);
+                         sp + L.b2, nullptr, 1, B, L.hid, L.hid, H, W, 1, st, nullptr, same);
     if (rc != FINC_OK)
         return rc;
-    if (9 * L.C >= 64 && L.hid >= 64)
+    if (same || 9 * L.C >= 64)
         return launch_conv_taps(s.t2, (long long)L.hid * hw, s.hh, (long long)L.C * hw,
                                 sp + L.w3, sp + L.b3, sp + L.ls3, B, L.hid, L.C, H, W, st,
                                 s.part);
@@ -490,7 +574,7 @@ int coupling_net(const float *v, long long vs, const float *sp, const StepLayout
 // log|det| (logdet may be null).
 int step_forward_dev(float *h, const float *x, double *logdet, const float *sp, const char *pp,
                      int B, int C, int H, int W, int k, int hid, const StepScratch &s,
-                     hipStream_t st) {
+                     const float *pk, hipStream_t st) {
     const StepLayout L = step_layout(C, k, hid);
     const StepPrep P = step_prep(C, k);
     const long long img = (long long)C * H * W;
@@ -500,7 +584,7 @@ int step_forward_dev(float *h, const float *x, double *logdet, const float *sp, 
         rc = launch_conv(s.u, img, h, img, lin + C * C + C, lin + 2 * C * C + C, nullptr, 0, B, C,
                          C, H, W, 1, st);
     if (rc == FINC_OK)
-        rc = coupling_net(h, img, sp, L, s, B, H, W, st);
+        rc = coupling_net(h, img, sp, L, s, B, H, W, pk, st);
     if (rc == FINC_OK)
         rc = launch_elt(0, h, img, nullptr, 0, s.hh, nullptr, logdet,
                         logdet ? (const double *)(pp + P.ld) : nullptr, B, L.Ch, H * W, st);
@@ -511,11 +595,12 @@ int step_forward_dev(float *h, const float *x, double *logdet, const float *sp, 
 // they differ), the inverse 1x1 / actnorm map into u, the unit's wavefront
 // inverse back into x.
 int step_inverse_dev(const float *y, float *x, const float *sp, const char *pp, int B, int C,
-                     int H, int W, int k, int hid, const StepScratch &s, hipStream_t st) {
+                     int H, int W, int k, int hid, const StepScratch &s, const float *pk,
+                     hipStream_t st) {
     const StepLayout L = step_layout(C, k, hid);
     const StepPrep P = step_prep(C, k);
     const long long img = (long long)C * H * W;
-    int rc = coupling_net(y, img, sp, L, s, B, H, W, st);
+    int rc = coupling_net(y, img, sp, L, s, B, H, W, pk, st);
     if (rc == FINC_OK)
         rc = launch_elt(1, x, img, y == x ? nullptr : y, img, s.hh, nullptr, nullptr, nullptr, B,
                         L.Ch, H * W, st);
@@ -655,7 +740,13 @@ int finc_step_forward(const float *x, float *y, double *logdet, const float *sp,
     if (B == 0)
         return FINC_OK;
     const StepScratch s = carve(workspace, B, C, H, W, hid);
-    return step_forward_dev(y, x, logdet, sp, (const char *)prepared, B, C, H, W, k, hid, s, stream);
+    const StepLayout L = step_layout(C, k, hid);
+    const int packed = net_room(L, B, H, W, 1);
+    const int rc = pack_nets(sp, L, s, packed, stream);
+    if (rc != FINC_OK)
+        return rc;
+    return step_forward_dev(y, x, logdet, sp, (const char *)prepared, B, C, H, W, k, hid, s,
+                            packed ? s.t1 : nullptr, stream);
 }
 
 int finc_step_inverse(const float *y, float *x, const float *sp, const void *prepared, int B,
@@ -665,7 +756,13 @@ int finc_step_inverse(const float *y, float *x, const float *sp, const void *pre
     if (B == 0)
         return FINC_OK;
     const StepScratch s = carve(workspace, B, C, H, W, hid);
-    return step_inverse_dev(y, x, sp, (const char *)prepared, B, C, H, W, k, hid, s, stream);
+    const StepLayout L = step_layout(C, k, hid);
+    const int packed = net_room(L, B, H, W, 1);
+    const int rc = pack_nets(sp, L, s, packed, stream);
+    if (rc != FINC_OK)
+        return rc;
+    return step_inverse_dev(y, x, sp, (const char *)prepared, B, C, H, W, k, hid, s,
+                            packed ? s.t1 : nullptr, stream);
 }
 
 size_t finc_flow_param_count(int L, int K, int C0, int k, int hid) {
@@ -769,8 +866,16 @@ int finc_flow_forward(const float *x, float *const *z, double *logdet, const flo
         rc = launch_squeeze(in, hA, B, Cin, 2 * H, 2 * W, in_stride, lev, 0, st);
         const StepLayout S = step_layout(C, k, hid);
         const StepScratch s = carve(scratch, B, C, H, W, hid);
+        const int room = net_room(S, B, H, W, K);   // packed networks at a time
+        const long long pf = net_shape(S).floats;
         for (int j = 0; j < K && rc == FINC_OK; ++j) {
-            rc = step_forward_dev(hA, hA, logdet, p, q, B, C, H, W, k, hid, s, st);
+            if (room && j % room == 0) {   // those of Steps j .. j + room - 1
+                rc = pack_nets(p, S, s, room < K - j ? room : K - j, st);
+                if (rc != FINC_OK)
+                    break;
+            }
+            rc = step_forward_dev(hA, hA, logdet, p, q, B, C, H, W, k, hid, s,
+                                  room ? s.t1 + (j % room) * pf : nullptr, st);
             p += S.total;
             q += step_prep(C, k).total;
         }
@@ -843,10 +948,18 @@ int finc_flow_sample(const float *const *z, float *x, const float *params, const
                 rc = launch_elt(2, hA, lev, nullptr, 0, s.hh, (float *)z[l], nullptr, nullptr, B,
                                 C / 2, H * W, st);
         }
+        const int room = net_room(S, B, H, W, K);   // packed networks at a time
+        const long long pf = net_shape(S).floats;
         for (int j = K - 1; j >= 0 && rc == FINC_OK; --j) {
+            if (room && (j == K - 1 || j % room == room - 1)) {   // those of Steps j / room * room .. j
+                const int first = j / room * room;
+                rc = pack_nets(lp[l] + (long long)first * S.total, S, s, j + 1 - first, st);
+                if (rc != FINC_OK)
+                    break;
+            }
             rc = step_inverse_dev(src, hA, lp[l] + (long long)j * S.total,
                                   lq[l] + (size_t)j * step_prep(C, k).total, B, C, H, W, k, hid, s,
-                                  st);
+                                  room ? s.t1 + (j % room) * pf : nullptr, st);
             src = hA;
         }
         if (rc != FINC_OK)

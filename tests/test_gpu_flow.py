@@ -73,6 +73,79 @@ def test_step(orc, case):
     assert torch.equal(finc.step_inverse(y[-1:].contiguous(), spd, prep, k, hid)[0], xr[-1])
 
 
+# edges of the coupling network's launches: 32-pixel and 32-channel tiles and
+# their remainders, one and two fragments a wave, up to 4 / more than 4 and
+# more than 8 fragments of tap rows, the widest hid in LDS and one beyond, and
+# the 128 x 128 tiles of the layers launched one by one
+NET_CASES = [
+    # (B, C, H, W, hid)
+    (1, 4, 1, 1, 1), (33, 12, 3, 3, 31), (40, 12, 5, 7, 257), (24, 16, 4, 5, 200),
+    (60, 24, 5, 5, 96), (23, 64, 4, 4, 64), (9, 12, 16, 16, 512), (1, 12, 5, 5, 512),
+    (3, 12, 9, 8, 513), (26, 8, 16, 16, 544),
+]
+
+
+@pytest.mark.parametrize("case", NET_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_step_network_edges(orc, case):
+    """The Step at the network's tile edges: two images against the oracle
+    (its error bound and fp32 rounding of the sums are far below TOL), and
+    every image the same bits alone as in its batch -- few pixels run the
+    layers one by one, many run them in one launch."""
+    B, C, H, W, hid = case
+    print(f"step network B={B} C={C} H={H} W={W} hid={hid}", flush=True)
+    sp = synth.step_params(C, 3, hid, seed=C + hid)
+    rng = np.random.default_rng(B + H)
+    y = rng.normal(size=(B, C, H, W))
+    spd, yd = dev(sp), dev(y)
+    prep = finc.step_prepare(spd, C, 3, hid)
+    x = finc.step_inverse(yd, spd, prep, 3, hid, out=poisoned(y.shape))
+    pick = sorted({0, B - 1})
+    assert_close(host(x)[pick], orc.step_inverse(f64(y)[pick], f64(sp), 3, hid), "step inverse")
+    for b in pick:
+        one = finc.step_inverse(yd[b:b + 1].contiguous(), spd, prep, 3, hid)
+        assert torch.equal(one[0], x[b]), f"image {b} alone"
+
+
+def test_step_network_not_finite(orc):
+    """Inputs whose products overflow 16 bits, and an infinite one, in one image
+    of 200: the other images' bits do not change, the image has the same bits
+    alone, and wherever the oracle is finite it agrees.  (The GPU's ReLU takes
+    NaN to 0, the oracle's keeps it.)  The unit, actnorm and 1x1 are the
+    identity, so only the network mixes values."""
+    B = 200
+    C, H, W, hid = 12, 4, 4, 96
+    sp = synth.step_params(C, 3, hid, seed=5)
+    n = 4 * 9 * 9
+    Kq4 = np.zeros((4, 3, 3, 3, 3))
+    for g in range(4):
+        sh, sw = synth.self_tap(g, 3)
+        Kq4[g, range(3), range(3), sh, sw] = 1.0
+    sp[:n] = Kq4.ravel()
+    sp[n:n + C], sp[n + C:n + 2 * C] = 1.0, 0.0
+    sp[n + 2 * C:n + 2 * C + C * C] = np.eye(C).ravel()
+    W1 = sp[n + 2 * C + C * C:][:hid * 6 * 9].reshape(hid, 6, 9)
+    W1[:, 0] *= 1e-31   # channel 0 carries the huge values
+    W1[:, 1] = 0.0      # channel 1 the infinite one: 0 times it is NaN
+    W2 = sp[n + 2 * C + C * C + hid * 54 + hid:][:hid * hid]
+    W2 *= 1e-7          # (the huge inputs' products are near 1e7)
+    y = np.random.default_rng(3).normal(size=(B, C, H, W))
+    spd = dev(sp)
+    prep = finc.step_prepare(spd, C, 3, hid)
+    clean = finc.step_inverse(dev(y), spd, prep, 3, hid)
+    y[0, 0, 1, 2], y[0, 0, 3, 0] = 3.4e38, -3.39e38
+    for what in ("huge inputs", "an infinite input"):
+        if what == "an infinite input":
+            y[0, 1, 0, 0] = np.inf
+        x = finc.step_inverse(dev(y), spd, prep, 3, hid)
+        assert torch.equal(x[1:], clean[1:]), what
+        one = finc.step_inverse(dev(y[:1]), spd, prep, 3, hid)
+        assert torch.equal(one[0].view(torch.int32), x[0].view(torch.int32)), what
+        want = orc.step_inverse(f64(y)[:1], f64(sp), 3, hid)
+        fin = np.isfinite(want)
+        assert fin.all() == (what == "huge inputs")
+        assert_close(np.where(fin, host(x[:1]), 0.0), np.where(fin, want, 0.0), what)
+
+
 def test_flow_small(orc):
     c = synth.flow_case(**synth.FLOWS["flow_small_L2_K2_b4"])
     a = dict(L=c["L"], K=c["K"], k=c["k"], hid=c["hid"])
