@@ -144,6 +144,28 @@ def test_actnorm_backward(orc, shape):
     assert all(torch.equal(a, b) for a, b in zip((dx, ds, db), again))
 
 
+@pytest.mark.parametrize("shape", [(1, 2, 1, 4), (5, 3, 3, 5), (3, 7, 9, 12), (9, 2, 64, 68),
+                                   (2, 1, 33, 131)], ids=lambda s: "x".join(map(str, s)))
+def test_actnorm_backward_wide_loads(orc, shape):
+    """Planes of a multiple of four values (16-byte loads) and others, fewer
+    values than threads, a remainder of the loads in flight; and the same from
+    buffers that are not 16-byte aligned."""
+    B, C, H, W = shape
+    rng = np.random.default_rng(H)
+    x, dy = rng.normal(size=shape), rng.normal(size=shape)
+    s = rng.uniform(0.5, 1.5, size=C)
+    got = finc.actnorm_backward(dev(x), dev(dy), dev(s), -0.25)
+    want = orc.actnorm_backward(f64(x), f64(dy), f64(s), -0.25)
+    for g, w, what in zip(got, want, ("dx", "ds", "db")):
+        assert_close(host(g), w, f"actnorm {what} {shape}")
+
+    def shifted(t):
+        return torch.cat([t.new_zeros(1), t.reshape(-1)])[1:].view(t.shape)
+    off = finc.actnorm_backward(shifted(dev(x)), shifted(dev(dy)), dev(s), -0.25)
+    for g, w, what in zip(off, want, ("dx", "ds", "db")):
+        assert_close(host(g), w, f"actnorm {what} {shape}, unaligned")
+
+
 @pytest.mark.parametrize("B", [1, 3, 100])
 def test_gauss_nll(orc, B):
     """Three latents of the CIFAR-10 flow's shapes ([28, 28, 28] with L = 3
