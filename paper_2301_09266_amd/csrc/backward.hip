@@ -353,12 +353,12 @@ __global__ __launch_bounds__(kAnThreads) void actnorm_bwd_kernel(const float *x,
     const int hv = HW / N, n = (b1 - b0) * hv;   // (fewer than 2^31 values in all)
     const float sc = s[c];
     double sx = 0.0, sy = 0.0;
-    for (int base = tid; base < n; base += kAnU * kAnThreads) {
+    for (unsigned base = tid; base < (unsigned)n; base += kAnU * kAnThreads) {
         V g[kAnU], v[kAnU];
         long long at[kAnU];
 #pragma unroll
         for (int u = 0; u < kAnU; ++u) {
-            const int i = min(base + u * kAnThreads, n - 1);
+            const int i = (int)min(base + u * kAnThreads, (unsigned)n - 1);
             const int b = divi(i, d_hv), p = i - b * hv;
             at[u] = ((long long)(b0 + b) * C + c) * hv + p;
             g[u] = reinterpret_cast<const V *>(dy)[at[u]];
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(kAnThreads) void actnorm_bwd_kernel(const float *x,
         }
 #pragma unroll
         for (int u = 0; u < kAnU; ++u) {
-            if (base + u * kAnThreads >= n)
+            if (base + u * kAnThreads >= (unsigned)n)
                 break;
             float *gv = reinterpret_cast<float *>(&g[u]);
             const float *xv = reinterpret_cast<const float *>(&v[u]);
