@@ -28,38 +28,18 @@
 #include <stdint.h>
 #include <string.h>
 
+#include "device_common.h"
 #include "finc.h"
+
+using namespace finc_detail;
 
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ inline f32x4 mfma4(float a, float b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
 inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 
-// Division of a non-negative int by a divisor fixed on the host (multiply-
-// high and shifts, Granlund and Montgomery's round-up method).
-struct Div {
-    unsigned m;
-    int s1, s2;
-};
-inline Div make_div(int d) {
-    int l = 0;
-    while ((1ull << l) < (unsigned long long)d)
-        ++l;
-    Div f;
-    f.m = (unsigned)((((1ull << l) - (unsigned long long)d) << 32) / (unsigned long long)d + 1);
-    f.s1 = l < 1 ? l : 1;
-    f.s2 = l > 1 ? l - 1 : 0;
-    return f;
-}
-__device__ inline int divi(int x, const Div &f) {
-    const unsigned t = __umulhi(f.m, (unsigned)x);
-    return (int)((t + (((unsigned)x - t) >> f.s1)) >> f.s2);
-}
+typedef FastDiv Div;
+inline Div make_div(int d) { return make_fastdiv(d); }
+__device__ inline int divi(int x, const Div &f) { return fdiv(x, f); }
 
 struct ConvArgs {
     const float *x;

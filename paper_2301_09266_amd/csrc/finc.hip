@@ -30,6 +30,7 @@
 #include <stdint.h>
 #include <string.h>
 
+#include "device_common.h"
 #include "finc.h"
 
 // The library is one translation unit, or several compiled in parallel:
@@ -39,6 +40,8 @@
 #ifndef FINC_PART
 #define FINC_PART -1
 #endif
+
+using namespace finc_detail;
 
 namespace {
 
@@ -51,29 +54,6 @@ __host__ __device__ inline int round_up4(int c) { return (c + 3) & ~3; }
 __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 __host__ __device__ inline int imin(int a, int b) { return a < b ? a : b; }
 __host__ __device__ inline int imax(int a, int b) { return a > b ? a : b; }
-
-// Division of a non-negative int by a divisor fixed on the host, as a
-// multiply-high and two shifts (Granlund and Montgomery's round-up method:
-// l = ceil(log2 d), m = floor(2^32 (2^l - d) / d) + 1; exact for every
-// 32-bit dividend).
-struct FastDiv {
-    unsigned m;
-    int s1, s2;
-};
-inline FastDiv make_fastdiv(int d) {
-    int l = 0;
-    while ((1ull << l) < (unsigned long long)d)
-        ++l;
-    FastDiv f;
-    f.m = (unsigned)((((1ull << l) - (unsigned long long)d) << 32) / (unsigned long long)d + 1);
-    f.s1 = l < 1 ? l : 1;
-    f.s2 = l > 1 ? l - 1 : 0;
-    return f;
-}
-__device__ inline int fdiv(int x, const FastDiv &f) {
-    const unsigned t = __umulhi(f.m, (unsigned)x);
-    return (int)((t + (((unsigned)x - t) >> f.s1)) >> f.s2);
-}
 
 // Pins a loaded value in a register at this point, so that the compiler
 // cannot move the load into the branch that uses it: a group of loads whose
@@ -455,10 +435,6 @@ __global__ __launch_bounds__(kWave) void logdet_kernel(const float *K, int n, in
 // of rows that must not land.  All pixel-major with the channel axis padded
 // to CP = 4 * ceil(C / 4).
 // ---------------------------------------------------------------------------
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-
-
 constexpr int kMaxWaves = 16;
 constexpr size_t kLdsBytes = 160 * 1024;   // LDS of a gfx950 workgroup
 constexpr int kMaxGroups = 8;                       // quad groups (x4 quads) per wave
@@ -607,10 +583,6 @@ inline bool make_plan(int C, int H, int W, int K, Plan &p, bool stream = false) 
         p.wave[w] = role | (tile % p.MT) << 2 | (tile / p.MT) << 6 | h << 10 | ng << 14;
     }
     return true;
-}
-
-__device__ inline f32x4 mfma4(float a, float b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
 // One level of an inverse chain: an input tensor, U units of `lpu` layers,
@@ -1915,6 +1887,8 @@ namespace {
 // each image into blocks of rows (with the k-1 halo rows) so that the grid
 // covers the chip; a unit keeps the image in LDS across its four layers.
 // ---------------------------------------------------------------------------
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
 struct FwdPlan {
     int C, CP, H, W, K, P, WP;
     int NT, ncq, nq, NG;         // channel tiles, quads per tile (all taps), quad groups
@@ -1934,6 +1908,8 @@ struct FwdPlan {
     // divisions of the index arithmetic: staged plane of a full and of the
     // last row block, WP, NGw, ncq, K, NT, W, CP / 4
     FastDiv d_plane, d_plane_last, d_WP, d_NGw, d_ncq, d_K, d_NT, d_W, d_cp4;
+    FastDiv d_KK, d_nwi;         // k^2; weight loads of a wave per channel tile, nwi
+    int nwi;
 };
 
 struct FwdArgs {
@@ -1950,20 +1926,21 @@ struct FwdArgs {
     FwdPlan fp;
 };
 
-constexpr int kFwdThreads = 256;
+constexpr int kFwdThreads = 256;       // (preparation blocks and single layers)
+constexpr int kFwdUnitThreads = 512;
 constexpr int kFwdMinBlocks = 256;   // a block per compute unit of the chip
 
-template <bool PADW>
-__global__ __launch_bounds__(kFwdThreads) void forward_kernel(FwdArgs a) {
-    extern __shared__ float sm[];
+// ROWS: how the weights reach LDS (units of several channel tiles; see below).
+template <bool PADW, bool ROWS>
+__device__ __forceinline__ void forward_block(const FwdArgs &a, const int block, float *sm) {
     const FwdPlan &fp = a.fp;
     const int nprep = a.split ? 4 : fp.n;   // layers prepared
     const int npre = a.prepared ? nprep * a.ppl : 0;
-    if ((int)blockIdx.x < npre) {
+    if (block < npre) {
         // the weights for the inverse, prepared by the launch's first blocks
         // (dispatched first: their latency chain is the longest; the forward
         // blocks do not wait for them)
-        const int pb = blockIdx.x, layer = pb / a.ppl, part = pb - layer * a.ppl;
+        const int pb = block, layer = pb / a.ppl, part = pb - layer * a.ppl;
         prep_columns<kFwdThreads>(a.K + (size_t)layer * fp.C * fp.C * fp.K * fp.K,
                                   a.prepared + (size_t)layer * prep_layer_floats(fp.C, fp.K),
                                   fp.C, fp.K, nprep == 1 ? fp.corner0 : layer, part * kFwdThreads,
@@ -1971,7 +1948,7 @@ __global__ __launch_bounds__(kFwdThreads) void forward_kernel(FwdArgs a) {
         return;
     }
     const int C = fp.C, CP = fp.CP, H = fp.H, W = fp.W, K = fp.K, P = fp.P, WP = fp.WP;
-    if (a.logdet && (int)blockIdx.x == npre) {
+    if (a.logdet && block == npre) {
         // log|det| on a block of its own (next after the preparation blocks,
         // so it is dispatched early and no forward block carries its fp64
         // logarithms): H W times the sum over the layers (or the four
@@ -1998,7 +1975,7 @@ __global__ __launch_bounds__(kFwdThreads) void forward_kernel(FwdArgs a) {
     const int lane = threadIdx.x & 63, kq = lane >> 4, li = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nwaves = blockDim.x >> 6;
-    const int bid = blockIdx.x - npre - (a.logdet ? 1 : 0);
+    const int bid = block - npre - (a.logdet ? 1 : 0);
     const int b = bid / fp.nblk, blk = bid - b * fp.nblk;
     const int corner0 = a.split ? (b & 3) : fp.corner0;   // this block's (first) corner
     const float *Kb = a.K + (a.split ? (size_t)(b & 3) * fp.C * fp.C * fp.K * fp.K : 0);
@@ -2007,20 +1984,26 @@ __global__ __launch_bounds__(kFwdThreads) void forward_kernel(FwdArgs a) {
     float4 *Wf = reinterpret_cast<float4 *>(sm + fp.offW);
     int *Dq = reinterpret_cast<int *>(sm + fp.offD);
     const size_t HW = (size_t)H * W;
-    const float *xb = a.in + (size_t)b * C * HW;
-    float *yb = a.out + (size_t)b * C * HW;
+    const size_t img = C * HW;
+    const float *xb = a.in + (size_t)b * img;
+    float *yb = a.out + (size_t)b * img;
     // weight fragments: Wf[(nt NGw + g) 64 + lane].e = K[co][ci][tap] for
     // co = 16 nt + li, quad u = 4 g + kq (tap u / ncq, ci = 4 (u % ncq) + e),
-    // the channel mask applied (self tap: ci <= co only).  A round is two
-    // fragments a thread: eight raw buffer loads over the layer's C^2 k^2
-    // floats at (co C + ci) k^2 + tap (entries that do not exist read past
-    // the end, which returns 0), all in flight before the stores.
+    // the channel mask applied (self tap, number selft of K: ci <= co only),
+    // zeros where a channel or quad does not exist.
+    const int K2 = K * K, ckk = C * K2;
+    const unsigned nrec = (unsigned)(C * ckk * 4);
+    auto krsrc = [&](int q) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(Kb + (size_t)q * C * ckk),
+                                                 (short)0, (int)nrec, kBufferWord3);
+    };
+    // One channel tile: fragment by fragment.  A round is two fragments a
+    // thread: eight raw buffer loads over the layer's C^2 k^2 floats at
+    // (co C + ci) k^2 + tap (entries that do not exist read past the end,
+    // which returns 0), all in flight before the stores.
     const int nfrag = fp.NT * fp.NGw * 64;
-    auto wload = [&](int q, int base, float(&v)[2][4]) {
-        const int K2 = K * K;
-        const unsigned nrec = (unsigned)(C * C * K2 * 4);
-        const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float *>(Kb + (size_t)q * C * C * K2), (short)0, (int)nrec, kBufferWord3);
+    auto gload = [&](int q, int base, float(&v)[2][4]) {
+        const __amdgpu_buffer_rsrc_t rk = krsrc(q);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int idx = base + h * blockDim.x;
@@ -2032,13 +2015,13 @@ __global__ __launch_bounds__(kFwdThreads) void forward_kernel(FwdArgs a) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int ci = 4 * cq + e;
-                const int off = ok && ci < C ? ((co * C + ci) * K2 + t) * 4 : (int)nrec;
+                const int at = (co * C + ci) * K2 + t;
+                const int off = ok && ci < C ? at * 4 : (int)nrec;
                 v[h][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rk, off, 0, 0));
             }
         }
     };
-    // the self tap (number selft) keeps ci <= co only
-    auto wstore = [&](float(&v)[2][4], int base, int selft) {
+    auto gstore = [&](float(&v)[2][4], int base, int selft) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int idx = base + h * blockDim.x;
@@ -2054,10 +2037,62 @@ __global__ __launch_bounds__(kFwdThreads) void forward_kernel(FwdArgs a) {
                 Wf[idx] = make_float4(v[h][0], v[h][1], v[h][2], v[h][3]);
         }
     };
+    // ROWS (several channel tiles): K as it lies in memory.  A load of a wave
+    // takes 64 bytes of each of 16 rows (rows of C k^2 floats), and each value
+    // goes to its fragment -- 256 bytes a quad, so its address is linear in the
+    // quad -- with a 4-byte LDS store.  Fragment by fragment a load of a wave
+    // meets 64 lines, eight of them in flight.  Units, with the wider workgroups
+    // of launch_forward: 24 x 16 x 16 38.5 -> 30.0 us, 48 x 8 x 8 69 -> 50 us
+    // (batch 64); a single layer, or one tile, has too few weights to gain
+    // (23 x 27 x 19 12.4 -> 15.0 us).
+    constexpr int kWU = 4;   // a wave's loads in flight
+    const int nwl = fp.NT * fp.nwi;
+    auto rload = [&](int q, int first, u32x4(&v)[kWU]) {
+        const __amdgpu_buffer_rsrc_t rk = krsrc(q);
+#pragma unroll
+        for (int h = 0; h < kWU; ++h) {
+            const int w = first + h * nwaves, nt = fdiv(w, fp.d_nwi), i = w - nt * fp.nwi;
+            const int row = nt * 16 + li;
+            const int off = w < nwl && row < C ? (row * ckk + 16 * i + 4 * kq) * 4 : (int)nrec;
+            v[h] = __builtin_amdgcn_raw_buffer_load_b128(rk, off, 0, 0);
+        }
+    };
+    auto rstore = [&](const u32x4(&v)[kWU], int first, int selft) {
+        float *Ws = sm + fp.offW;
+#pragma unroll
+        for (int h = 0; h < kWU; ++h) {
+            const int w = first + h * nwaves, nt = fdiv(w, fp.d_nwi), i = w - nt * fp.nwi;
+            const int row = nt * 16 + li;
+            if (w >= nwl || row >= C)
+                continue;
+            int kk = 16 * i + 4 * kq, c = fdiv(kk, fp.d_KK), t = kk - c * K2;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (kk < ckk) {
+                    const float x = t == selft && c > row ? 0.0f : __uint_as_float(v[h][e]);
+                    const int u = t * fp.ncq + (c >> 2);
+                    Ws[(nt * fp.NGw * 4 + u) * 64 + li * 4 + (c & 3)] = x;
+                }
+                ++kk;
+                if (++t == K2) {
+                    t = 0;
+                    ++c;
+                }
+            }
+        }
+    };
     // the first layer's first round of weights goes out ahead of the input,
-    // so that one memory latency covers both
-    float wpre[2][4];
-    wload(0, threadIdx.x, wpre);
+    // so that one memory latency covers both (ROWS: a later layer's ahead of
+    // the products of the one before)
+    float gpre[2][4];
+    u32x4 rpre[kWU];
+    if constexpr (ROWS) {
+        rload(0, wave, rpre);
+        for (int i = threadIdx.x; i < nfrag + (PADW ? 0 : 64); i += blockDim.x)
+            Wf[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    } else {
+        gload(0, threadIdx.x, gpre);
+    }
     // zero-bordered input rows i0 - HB .. i0 + rb + HB - 1: every element of
     // the block is written once, with x where the taps of this launch read
     // the image and zero elsewhere (outside the image, padding channels, and
@@ -2141,23 +2176,34 @@ __global__ __launch_bounds__(kFwdThreads) void forward_kernel(FwdArgs a) {
         const int corner = fp.n == 1 ? corner0 : q;
         int oh, ow;
         self_tap(corner, K, oh, ow);
-        const int nfrag = fp.NT * fp.NGw * 64;
-        int wb = threadIdx.x;
-        if (q == 0) {   // (the first round went out before the input)
-            wstore(wpre, wb, oh * K + ow);
-            wb += 2 * blockDim.x;
-            if (!PADW && threadIdx.x < 64)   // the padding groups' zero fragment
-                Wf[nfrag + threadIdx.x] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        }
-        for (; wb < nfrag; wb += 2 * blockDim.x) {
-            float v[2][4];
-            wload(q, wb, v);
+        const int selft = oh * K + ow;
+        if constexpr (ROWS) {
+            if (q == 0)
+                __syncthreads();   // the fragments' zeros
+            rstore(rpre, wave, selft);
+            for (int w = wave + kWU * nwaves; w < nwl; w += kWU * nwaves) {
+                u32x4 v[kWU];
+                rload(q, w, v);
+                rstore(v, w, selft);
+            }
+        } else {
+            int wb = threadIdx.x;
+            if (q == 0) {   // (the first round went out before the input)
+                gstore(gpre, wb, selft);
+                wb += 2 * blockDim.x;
+                if (!PADW && threadIdx.x < 64)   // the padding groups' zero fragment
+                    Wf[nfrag + threadIdx.x] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            }
+            for (; wb < nfrag; wb += 2 * blockDim.x) {
+                float v[2][4];
+                gload(q, wb, v);
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+                for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    pin(v[h][e]);
-            wstore(v, wb, oh * K + ow);
+                    for (int e = 0; e < 4; ++e)
+                        pin(v[h][e]);
+                gstore(v, wb, selft);
+            }
         }
         // gather offset of quad u relative to the output pixel's address (taps
         // reach up/left too: offsets are signed); padding quads, whose
@@ -2169,6 +2215,8 @@ __global__ __launch_bounds__(kFwdThreads) void forward_kernel(FwdArgs a) {
         }
         __syncthreads();
         const bool last = q == fp.n - 1;
+        if (ROWS && !last)
+            rload(q + 1, wave, rpre);
         float *Yo = sm + fp.offO;
         // rows of this layer's output the block computes, rlo .. rhi - 1: its
         // own, and in a band of a unit also those its later layers read
@@ -2248,6 +2296,13 @@ __global__ __launch_bounds__(kFwdThreads) void forward_kernel(FwdArgs a) {
 // ---------------------------------------------------------------------------
 // Host side.
 // ---------------------------------------------------------------------------
+
+template <bool PADW, bool ROWS, int MAXT>
+__global__ __launch_bounds__(MAXT) void forward_kernel(FwdArgs a) {
+    extern __shared__ float sm[];
+    forward_block<PADW, ROWS>(a, blockIdx.x, sm);
+}
+
 bool valid_shape(int B, int C, int H, int W, int k) {
     if (B < 0 || C < 1 || C > FINC_MAX_C || H < 1 || W < 1 || k < 1 || k > FINC_MAX_K)
         return false;
@@ -2368,6 +2423,9 @@ FwdPlan make_fwd_plan(int C, int H, int W, int K, int n, int corner0, int B, boo
     p.d_plane_last = make_fastdiv((rb_last + 2 * p.HB) * p.WP);
     p.d_WP = make_fastdiv(p.WP);
     p.d_NGw = make_fastdiv(p.NGw);
+    p.d_KK = make_fastdiv(K * K);
+    p.nwi = ceil_div(C * K * K, 16);
+    p.d_nwi = make_fastdiv(p.nwi);
     p.d_ncq = make_fastdiv(p.ncq);
     p.d_K = make_fastdiv(K);
     p.d_NT = make_fastdiv(p.NT);
@@ -2730,15 +2788,28 @@ int launch_forward(const float *x, float *y, const float *K, double *logdet, flo
     int rc = check_lds(lds);
     if (rc != FINC_OK)
         return rc;
-    const void *fk = a.fp.padw ? reinterpret_cast<const void *>(forward_kernel<true>)
-                               : reinterpret_cast<const void *>(forward_kernel<false>);
+    // A unit whose grid leaves a compute unit at most one block (and whose
+    // preparation blocks are not of kFwdThreads) takes twice the waves: a block's
+    // four phases then have two a SIMD (12 x 32 x 32, batch 64: k = 3 29.1 ->
+    // 27.2 us, k = 5 63.8 -> 58.6 us).
+    const bool wide = n > 1 && !fuse && B * a.fp.nblk <= kFwdMinBlocks;
+    const int threads = wide ? kFwdUnitThreads : kFwdThreads;
+    auto pick = [&](auto padw) -> const void * {
+        constexpr bool P = decltype(padw)::value;
+        if (n > 1 && a.fp.NT > 1)
+            return wide ? reinterpret_cast<const void *>(forward_kernel<P, true, kFwdUnitThreads>)
+                        : reinterpret_cast<const void *>(forward_kernel<P, true, kFwdThreads>);
+        return wide ? reinterpret_cast<const void *>(forward_kernel<P, false, kFwdUnitThreads>)
+                    : reinterpret_cast<const void *>(forward_kernel<P, false, kFwdThreads>);
+    };
+    const void *fk = a.fp.padw ? pick(std::true_type{}) : pick(std::false_type{});
     if (hipFuncSetAttribute(fk,
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         (void)hipGetLastError();   // not needed on every runtime; the launch check decides
     // preparation blocks, then the log|det| block, then the forward blocks
     const unsigned blocks = (unsigned)(a.nfwd + (fuse ? nprep * a.ppl : 0) + (logdet ? 1 : 0));
     void *args[] = {&a};
-    (void)hipLaunchKernel(fk, dim3(blocks), dim3(kFwdThreads), args, lds, stream);
+    (void)hipLaunchKernel(fk, dim3(blocks), dim3(threads), args, lds, stream);
     rc = launched();
     if (rc != FINC_OK || !prepared || fuse)
         return rc;

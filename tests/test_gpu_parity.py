@@ -343,6 +343,26 @@ def test_unit_forward_bands(orc, shape):
     assert torch.equal(inplace, y)
 
 
+@pytest.mark.parametrize("shape", [(2, 16, 7, 6, 3), (2, 17, 6, 5, 3), (260, 17, 3, 4, 3),
+                                   (2, 33, 3, 3, 1), (2, 33, 5, 6, 4), (257, 20, 4, 4, 2),
+                                   (2, 57, 4, 4, 3), (260, 57, 2, 3, 3)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_unit_forward_weight_rows(orc, shape):
+    """Unit forward of several channel tiles, whose weights are read in memory
+    order: rows of C k^2 values that are and are not multiples of a load's
+    four, tiles of one channel, shared padding fragments (57 channels), and
+    blocks of 512 threads (up to 256 blocks) and of 256."""
+    B, C, H, W, k = shape
+    c = synth.unit_case(B, C, H, W, k)
+    print("unit forward", shape, flush=True)
+    K4 = np.stack([synth.garbage_in_mask(c["K4"][q], q, seed=q) for q in range(4)])
+    y = finc.unit_forward(dev(c["x"]), dev(K4), out=poisoned(c["x"].shape))
+    assert_close(host(y), orc.unit_forward(f64(c["x"]), f64(K4)), f"unit forward {shape}")
+    inplace = dev(c["x"])
+    finc.unit_forward(inplace, dev(K4), out=inplace)
+    assert torch.equal(inplace, y)
+
+
 @pytest.mark.parametrize("shape", [(2, 3, 5, 7, 3), (3, 12, 16, 16, 3), (1, 7, 9, 6, 5),
                                    (2, 4, 6, 6, 1), (2, 5, 8, 11, 2), (1, 20, 9, 10, 7),
                                    (2, 64, 5, 6, 3), (1, 33, 7, 5, 4), (3, 2, 11, 4, 6)],
