@@ -8,23 +8,24 @@
 // output gradient dy:
 //   dx[ci, s, t] = sum_{co, a, b} K[co][ci][a][b] dy[co, s - a + oh, t - b + ow]
 //     -- a convolution of dy with the kernel transposed over channels and
-//     flipped in space, run by the implicit-GEMM convolution of conv_gemm.h
-//     reading K that way (tap a' = k-1-a reads row s + a' - (k-1-oh));
+//     flipped in space: the forward of that kernel with the opposite corner
+//     (layer_dx of finc_detail.h);
 //   dK[co][ci][a][b] = sum over images and pixels of dy[co, i, j] times the
 //     input the tap read (zero outside the image) -- a GEMM with
 //     M = C_out, N = C_in k^2 and a reduction over the B H W positions, in
-//     parts of the positions.
-// The two are independent: one launch (backward_kernel) runs the tiles of
-// both, and dk_reduce_kernel then adds dK's parts in order, sets the masked
-// entries to 0 and adds the log|det| term gld H W / K[c][c][self] on the
-// self diagonal.
+//     parts of the positions (dk_kernel), which dk_reduce_kernel adds in
+//     order, sets the masked entries to 0 and adds the log|det| term
+//     gld H W / K[c][c][self] on the self diagonal.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
 #include <string.h>
+#include <type_traits>
 
 #include "conv_gemm.h"
+#include "dk_tile.h"
 #include "finc.h"
+#include "finc_detail.h"
 
 namespace {
 
@@ -35,165 +36,43 @@ inline bool overlapb(const void *a, size_t na, const void *b, size_t nb) {
     return x < y + nb && y < x + na;
 }
 
-// dK as a GEMM over positions.  Block: 16 c_out x 64 columns (column =
-// ci k^2 + a k + b), 4 waves; every chunk of 64 positions (flattened over the
-// batch) is staged in LDS -- dy[co][pos] and the gathered inputs
-// x_tap[col][pos], both position-contiguous -- and wave w takes positions
-// 16 w .. 16 w + 15 of it (lane group kq: 4 consecutive positions, one
-// float4 per operand for four MFMAs).  The four waves' sums are added in
-// order through LDS; part z covers chunks [z cpp, (z+1) cpp)
-// and writes its sums to partial + z C (C k^2).
-struct DkArgs {
-    const float *x, *dy;
-    float *partial;
-    long long img;   // floats from one image to the next (x and dy)
-    int B, C, H, W, k, oh, ow, N, cpp, nchunk;
-    Div d_HW, d_W, d_kk, d_k;
-};
-
-constexpr int kDkLdsFloats = 80 * kSK;   // As (16 rows), Bs (64 rows); red reuses it
-
-__device__ __forceinline__ void dk_tile(const DkArgs &a, int bx, int by, int bz, float *lds) {
-    float *As = lds, *Bs = lds + 16 * kSK;
-    float(*red)[16][65] = reinterpret_cast<float(*)[16][65]>(lds);
-    const int tid = threadIdx.x, lane = tid & 63, kq = lane >> 4, li = lane & 15, wave = tid >> 6;
-    const int col0 = bx * 64, co0 = by * 16;
-    const int HW = a.H * a.W, P = a.B * HW, kk = a.k * a.k;
-    const long long img = a.img;
-    // staging roles: A: thread -> (co 16 x position quad 16); B: thread -> (col, 4 quads)
-    const int aco = co0 + (tid >> 4), aq = tid & 15;
-    const int bcol = col0 + (tid & 63), bq0 = tid >> 6;
-    const bool colok = bcol < a.N;
-    const int bci = colok ? divi(bcol, a.d_kk) : 0;
-    const int bt = colok ? bcol - bci * kk : 0;
-    const int ba = divi(bt, a.d_k), bb = bt - ba * a.k;
-    float ra[4], rb[4][4];
-    auto load_chunk = [&](int c) {
-        const int p0 = c * 64;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int pos = p0 + 4 * aq + e;
-            const bool ok = pos < P && aco < a.C;
-            const int n = ok ? divi(pos, a.d_HW) : 0, p = ok ? pos - n * HW : 0;
-            const float v = a.dy[ok ? n * img + (long long)aco * HW + p : 0];
-            ra[e] = ok ? v : 0.0f;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int pos = p0 + 4 * (bq0 + 4 * u) + e;
-                const bool pok = pos < P && colok;
-                const int n = pok ? divi(pos, a.d_HW) : 0, p = pok ? pos - n * HW : 0;
-                const int i = divi(p, a.d_W), j = p - i * a.W;
-                const int ii = i + ba - a.oh, jj = j + bb - a.ow;
-                const bool ok = pok && ii >= 0 && ii < a.H && jj >= 0 && jj < a.W;
-                const float v = a.x[ok ? n * img + (long long)bci * HW + ii * a.W + jj : 0];
-                rb[u][e] = ok ? v : 0.0f;
-            }
-        }
-    };
-    auto store_chunk = [&] {
-        *reinterpret_cast<float4 *>(&As[(tid >> 4) * kSK + 4 * aq]) =
-            make_float4(ra[0], ra[1], ra[2], ra[3]);
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            *reinterpret_cast<float4 *>(&Bs[(tid & 63) * kSK + 4 * (bq0 + 4 * u)]) =
-                make_float4(rb[u][0], rb[u][1], rb[u][2], rb[u][3]);
-    };
-    f32x4 acc[4];
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-        acc[s] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    const int c0 = bz * a.cpp, c1 = min(c0 + a.cpp, a.nchunk);
-    if (c0 < c1) {
-        load_chunk(c0);
-        store_chunk();
-    }
-    __syncthreads();
-    for (int c = c0; c < c1; ++c) {
-        if (c + 1 < c1)
-            load_chunk(c + 1);
-        const float4 w4 = *reinterpret_cast<const float4 *>(&As[li * kSK + 16 * wave + 4 * kq]);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const float4 b4 =
-                *reinterpret_cast<const float4 *>(&Bs[(16 * s + li) * kSK + 16 * wave + 4 * kq]);
-            acc[s] = mfma4(w4.x, b4.x, acc[s]);
-            acc[s] = mfma4(w4.y, b4.y, acc[s]);
-            acc[s] = mfma4(w4.z, b4.z, acc[s]);
-            acc[s] = mfma4(w4.w, b4.w, acc[s]);
-        }
-        if (c + 1 < c1) {
-            __syncthreads();
-            store_chunk();
-            __syncthreads();
-        }
-    }
-    // lane (kq, li) of wave w holds D[co 4 kq + rr][col 16 s + li]
-    __syncthreads();   // every wave's last reads of As / Bs are done
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr)
-            red[wave][4 * kq + rr][16 * s + li] = acc[s][rr];
-    __syncthreads();
-    float *pz = a.partial + (long long)bz * a.C * a.N;
-    for (int e = tid; e < 16 * 64; e += 256) {
-        const int r = e >> 6, cl = e & 63;
-        const int co = co0 + r, col = col0 + cl;
-        if (co < a.C && col < a.N)
-            pz[(long long)co * a.N + col] =
-                ((red[0][r][cl] + red[1][r][cl]) + red[2][r][cl]) + red[3][r][cl];
-    }
+// dK's blocks alone (dK without dx, and images of 2 GB or more).
+template <int K, bool BIG>
+__global__ __launch_bounds__(256) void dk_kernel(DkArgs a) {
+    __shared__ __attribute__((aligned(16))) float lds[dk_lds_floats<K>()];
+    dk_tile<K, BIG>(a, blockIdx.x, lds);
 }
 
-// One launch for both gradients, which are independent of each other:
-// blocks [0, ndx) are tiles of the input gradient's convolution (gx of them
-// along the pixels), the others tiles of dK's GEMM (dgx along its columns,
-// dgy along c_out, then the parts of the positions).
-template <int R, int WCO, int NS>
-__global__ __launch_bounds__(256) void backward_kernel(ConvArgs ca, int ndx, int gx, DkArgs da,
-                                                       int dgx, int dgy) {
-    constexpr int nc = conv_lds_floats<WCO, NS>();
-    __shared__ __attribute__((aligned(16))) float lds[nc > kDkLdsFloats ? nc : kDkLdsFloats];
-    int b = blockIdx.x;
-    if (b < ndx) {
-        conv_tile<R, WCO, NS>(ca, b % gx, b / gx, 0, lds);
-        return;
-    }
-    b -= ndx;
-    dk_tile(da, b % dgx, (b / dgx) % dgy, b / (dgx * dgy), lds);
-}
-
-// dK = the sum of the parts, in a fixed order: lane l of a group of 32
-// threads adds parts l, l + 32, l + 64, ... in turn, then the 32 lane sums
-// meet in a fixed butterfly; masked entries 0; gld H W / K[c][c][self] added
-// on the self diagonal (in fp64).  8 outputs per block of 256 threads.
+// dK = the sum of the parts, in a fixed order: of the eight groups of 32 threads
+// of a block, group g adds parts g, g + 8, g + 16, ... of 32 neighbouring
+// entries in turn, then the groups' sums in order.
 __global__ __launch_bounds__(256) void dk_reduce_kernel(const float *partial, int parts,
                                                         const float *K, float *dK, double gld,
                                                         int C, int k, int H, int W, int oh,
                                                         int ow) {
+    __shared__ float red[8][33];
     const int N = C * k * k, n = C * N;
-    const int e = blockIdx.x * 8 + (threadIdx.x >> 5), l = threadIdx.x & 31;
+    const int l = threadIdx.x & 31, g = threadIdx.x >> 5, e = blockIdx.x * 32 + l;
     const int ec = e < n ? e : n - 1;
     float v = 0.0f;
-    for (int z = l; z < parts; z += 32)
-        v += partial[(long long)z * n + ec];
+    for (int z = g; z < parts; z += 64) {
+        float p[8];
 #pragma unroll
-    for (int off = 16; off > 0; off >>= 1)
-        v += __shfl_xor(v, off, 32);
-    if (l != 0 || e >= n)
+        for (int u = 0; u < 8; ++u)
+            p[u] = partial[(long long)min(z + 8 * u, parts - 1) * n + ec];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            v += z + 8 * u < parts ? p[u] : 0.0f;
+    }
+    red[g][l] = v;
+    __syncthreads();
+    if (g != 0 || e >= n)
         return;
+#pragma unroll
+    for (int u = 1; u < 8; ++u)
+        v += red[u][l];
     const int co = e / N, col = e - co * N, ci = col / (k * k), t = col - ci * k * k;
-    const int a = t / k, b = t - a * k;
-    const bool self = a == oh && b == ow;
-    if (self && ci > co)
-        v = 0.0f;   // masked: its gradient is reset to zero
-    else if (self && ci == co)
-        v = (float)((double)v + gld * (double)H * (double)W /
-                                    (double)K[((co * C + co) * k + a) * k + b]);
-    dK[e] = v;
+    dK[e] = dk_entry(v, co, ci, t, K, gld, C, k, H, W, oh, ow);
 }
 
 // Parts of the position reduction: at least 2 chunks of 64 positions each,
@@ -217,25 +96,52 @@ bool valid_bwd_shape(int B, int C, int H, int W, int k) {
     return (long long)B * C * H * W < (1ll << 31);
 }
 
+// Both gradients where the forward's row blocks do not fit in LDS (very wide
+// rows, or many channels with a wide kernel): dx as the implicit GEMM of
+// conv_gemm.h on K read transposed and flipped, beside dK's blocks (da.blocks of
+// them, or none).  dx in tiles of 64 c_out x 64 pixels at 64 channels, else
+// 16 x 128, or 16 x 64 while there are fewer than two blocks a compute unit.
 template <int R, int WCO, int NS>
-void launch_fused(const ConvArgs &ca, int ndx, int gx, const DkArgs &da, int dgx, int dgy, int ndk,
-                  hipStream_t st) {
-    hipLaunchKernelGGL((backward_kernel<R, WCO, NS>), dim3(ndx + ndk), dim3(256), 0, st, ca, ndx,
-                       gx, da, dgx, dgy);
+__global__ __launch_bounds__(256) void gemm_grad_kernel(ConvArgs ca, int gx, DkArgs da) {
+    constexpr int nc = conv_lds_floats<WCO, NS>(), nd = dk_lds_floats<R>();
+    __shared__ __attribute__((aligned(16))) float lds[nc > nd ? nc : nd];
+    if ((int)blockIdx.x < da.blocks) {
+        dk_tile<R, false>(da, blockIdx.x, lds);
+        return;
+    }
+    const int b = blockIdx.x - da.blocks;
+    conv_tile<R, WCO, NS>(ca, b % gx, b / gx, 0, lds);
+}
+template <int R>
+void launch_gemm_grad(const ConvArgs &a, const DkArgs &da, hipStream_t st) {
+    const long long Q = (long long)a.B * a.H * a.W;
+    const int gy = cdiv(a.Co, 16);
+    auto go = [&](auto wco, auto ns) {
+        constexpr int WCO = decltype(wco)::value, NS = decltype(ns)::value;
+        const int gx = cdiv(Q, 16 * NS * (4 / WCO)), g = gx * cdiv(a.Co, 16 * WCO);
+        hipLaunchKernelGGL((gemm_grad_kernel<R, WCO, NS>), dim3(da.blocks + g), dim3(kConvThreads),
+                           0, st, a, gx, da);
+    };
+    if (a.Co >= 64 && cdiv(Q, 64) >= 256)
+        go(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+    else if ((long long)cdiv(Q, 128) * gy >= 512)
+        go(std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
+    else
+        go(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{});
 }
 
-// The instance for kernel size R and the convolution's tile configuration:
-// 64 c_out x 64 pixels at 64 channels, else 16 c_out x 32 pixels per wave
-// (NS = 2) when that still gives 256 tiles, else 16 x 16 (NS = 1).
-template <int R>
-void launch_fused_r(const ConvArgs &ca, int cfg, int ndx, int gx, const DkArgs &da, int dgx,
-                    int dgy, int ndk, hipStream_t st) {
-    if (cfg == 2)
-        launch_fused<R, 4, 4>(ca, ndx, gx, da, dgx, dgy, ndk, st);
-    else if (cfg == 1)
-        launch_fused<R, 1, 2>(ca, ndx, gx, da, dgx, dgy, ndk, st);
-    else
-        launch_fused<R, 1, 1>(ca, ndx, gx, da, dgx, dgy, ndk, st);
+// f(integral constant k) for 1 <= k <= 7.
+template <typename F>
+void for_k(int k, F f) {
+    switch (k) {
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 5: f(std::integral_constant<int, 5>{}); break;
+    case 6: f(std::integral_constant<int, 6>{}); break;
+    default: f(std::integral_constant<int, 7>{}); break;
+    }
 }
 
 // Both gradients of one layer whose images lie img floats apart in x, dy and
@@ -248,79 +154,84 @@ int launch_layer_backward(const float *x, const float *dy, const float *K, float
     const int oh = (corner == FINC_TL || corner == FINC_TR) ? k - 1 : 0;
     const int ow = (corner == FINC_TL || corner == FINC_BL) ? k - 1 : 0;
     const int n = C * C * k * k;
-    const long long Q = (long long)B * H * W;
-    // the input gradient: the convolution of dy with K transposed and flipped
-    ConvArgs ca;
-    memset(&ca, 0, sizeof(ca));
-    int cfg = 0, gx = 0, ndx = 0;
-    if (dx && B > 0) {
-        ca.x = dy;
-        ca.y = dx;
-        ca.Wt = K;
-        ca.B = B;
-        ca.Ci = C;
-        ca.Co = C;
-        ca.H = H;
-        ca.W = W;
-        ca.K = C * k * k;
-        ca.ph = k - 1 - oh;
-        ca.pw = k - 1 - ow;
-        ca.xs = ca.ys = img;
-        ca.d_HW = make_div(H * W);
-        ca.d_W = make_div(W);
-        ca.flip = 1;
-        ca.fself = oh * k + ow;
-        cfg = C >= 64 ? 2 : cdiv(Q, 128) >= 256 ? 1 : 0;
-        const int bn = cfg == 2 ? 64 : cfg == 1 ? 128 : 64, bm = cfg == 2 ? 64 : 16;
-        gx = cdiv(Q, bn);
-        ndx = gx * cdiv(C, bm);
-    }
-    // dK's partial sums over parts of the positions
+    // dK, in partial sums over parts of the positions
+    int parts = 0;
     DkArgs da;
     memset(&da, 0, sizeof(da));
-    int parts = 0, dgx = 1, dgy = 1, ndk = 0;
     if (dK && B > 0) {
-        parts = dk_parts(B, C, H, W, k);
         da.x = x;
         da.dy = dy;
+        da.K = K;
         da.partial = partial;
+        da.gld = gld;
         da.img = img;
-        da.B = B;
         da.C = C;
         da.H = H;
         da.W = W;
-        da.k = k;
         da.oh = oh;
         da.ow = ow;
         da.N = C * k * k;
-        da.nchunk = cdiv(Q, 64);
-        da.cpp = cdiv(da.nchunk, parts);
-        parts = cdiv(da.nchunk, da.cpp);
-        da.d_HW = make_div(H * W);
-        da.d_W = make_div(W);
-        da.d_kk = make_div(k * k);
-        da.d_k = make_div(k);
-        dgx = cdiv(da.N, 64);
-        dgy = cdiv(C, 16);
-        ndk = dgx * dgy * parts;
+        da.nt = cdiv(C, 16);
+        const int groups = cdiv(k * k, dk_taps(k));
+        // bands of up to 256 positions, cut, to no less than 64, while there are
+        // fewer blocks than compute units
+        da.WB = W < 32 ? W : 32;
+        da.bx = cdiv(W, da.WB);
+        da.RB = kDkPos / da.WB < 32 ? kDkPos / da.WB : 32;
+        if (da.RB > H)
+            da.RB = H;
+        while (da.RB > 1 && da.RB * da.WB > 64 &&
+               (long long)B * cdiv(H, da.RB) * da.bx * da.nt * da.nt * groups < 256)
+            da.RB = (da.RB + 1) / 2;
+        da.nbi = cdiv(H, da.RB) * da.bx;
+        da.nb = B * da.nbi;
+        parts = dk_parts(B, C, H, W, k);
+        da.bpp = cdiv(da.nb, parts);
+        parts = cdiv(da.nb, da.bpp);
+        da.dK = parts == 1 ? dK : nullptr;
+        const int wlast = W - (da.bx - 1) * da.WB;
+        da.d_nbi = make_div(da.nbi);
+        da.d_bx = make_div(da.bx);
+        da.d_nt = make_div(da.nt);
+        da.d_w = make_div(da.WB);
+        da.d_wl = make_div(wlast);
+        da.d_xw = make_div(da.WB + k - 1);
+        da.d_xwl = make_div(wlast + k - 1);
+        da.parts = parts;
+        da.d_nt2 = make_div(da.nt * da.nt);
+        da.d_parts = make_div(parts);
+        da.blocks = da.nt * da.nt * parts * groups;
     }
-    if (ndx + ndk > 0) {
-        switch (k) {
-        case 1: launch_fused_r<1>(ca, cfg, ndx, gx, da, dgx, dgy, ndk, stream); break;
-        case 2: launch_fused_r<2>(ca, cfg, ndx, gx, da, dgx, dgy, ndk, stream); break;
-        case 3: launch_fused_r<3>(ca, cfg, ndx, gx, da, dgx, dgy, ndk, stream); break;
-        case 4: launch_fused_r<4>(ca, cfg, ndx, gx, da, dgx, dgy, ndk, stream); break;
-        case 5: launch_fused_r<5>(ca, cfg, ndx, gx, da, dgx, dgy, ndk, stream); break;
-        case 6: launch_fused_r<6>(ca, cfg, ndx, gx, da, dgx, dgy, ndk, stream); break;
-        default: launch_fused_r<7>(ca, cfg, ndx, gx, da, dgx, dgy, ndk, stream); break;
+    // one launch for both, but for images of 2 GB or more
+    const bool big = (long long)C * H * W * 4 >= (1ll << 31);
+    const DkArgs none = {};
+    const DkArgs &beside = big ? none : da;
+    int rc = FINC_OK;
+    if (dx && B > 0) {
+        rc = layer_grads(dy, dx, K, B, C, H, W, k, corner, img, beside, stream);
+        if (rc == FINC_EUNSUPPORTED) {
+            ConvArgs ca = conv_args(dy, img, dx, img, K, nullptr, nullptr, 0, B, C, C, H, W, k);
+            ca.ph = k - 1 - oh;
+            ca.pw = k - 1 - ow;
+            ca.flip = 1;
+            ca.fself = oh * k + ow;
+            for_k(k, [&](auto kc) { launch_gemm_grad<decltype(kc)::value>(ca, beside, stream); });
+            rc = conv_launched();
         }
-        const int rc = conv_launched();
-        if (rc != FINC_OK)
-            return rc;
     }
-    if (!dK)
-        return FINC_OK;
-    hipLaunchKernelGGL(dk_reduce_kernel, dim3((n + 7) / 8), dim3(256), 0, stream, partial, parts,
+    if (rc == FINC_OK && da.blocks > 0 && (big || !dx)) {
+        for_k(k, [&](auto kc) {
+            constexpr int KC = decltype(kc)::value;
+            if (big)
+                hipLaunchKernelGGL((dk_kernel<KC, true>), dim3(da.blocks), dim3(256), 0, stream, da);
+            else
+                hipLaunchKernelGGL((dk_kernel<KC, false>), dim3(da.blocks), dim3(256), 0, stream, da);
+        });
+        rc = conv_launched();
+    }
+    if (rc != FINC_OK || !dK || parts == 1)
+        return rc;
+    hipLaunchKernelGGL(dk_reduce_kernel, dim3((n + 31) / 32), dim3(256), 0, stream, partial, parts,
                        K, dK, gld, C, k, H, W, oh, ow);
     return conv_launched();
 }

@@ -31,7 +31,9 @@
 #include <string.h>
 
 #include "device_common.h"
+#include "dk_tile.h"
 #include "finc.h"
+#include "finc_detail.h"
 
 // The library is one translation unit, or several compiled in parallel:
 // FINC_PART = g (0 <= g < kInverseGroups) holds only the inverse kernel
@@ -1923,6 +1925,7 @@ struct FwdArgs {
     // b' = 4 b + g is quarter g, with corner g and weights K + g C^2 k^2 (one
     // layer per block; four layers prepared)
     int split;
+    long long img;   // (FLIP) floats from one image to the next, in and out
     FwdPlan fp;
 };
 
@@ -1931,7 +1934,10 @@ constexpr int kFwdUnitThreads = 512;
 constexpr int kFwdMinBlocks = 256;   // a block per compute unit of the chip
 
 // ROWS: how the weights reach LDS (units of several channel tiles; see below).
-template <bool PADW, bool ROWS>
+// FLIP (one layer): K read transposed over channels and reversed in space,
+// K'[n][m][t] = K[m][n][k^2 - 1 - t], with K's masked entries zero: the layer's
+// input gradient is the forward of K' with the opposite corner.
+template <bool PADW, bool ROWS, bool FLIP>
 __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block, float *sm) {
     const FwdPlan &fp = a.fp;
     const int nprep = a.split ? 4 : fp.n;   // layers prepared
@@ -1984,7 +1990,7 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
     float4 *Wf = reinterpret_cast<float4 *>(sm + fp.offW);
     int *Dq = reinterpret_cast<int *>(sm + fp.offD);
     const size_t HW = (size_t)H * W;
-    const size_t img = C * HW;
+    const size_t img = FLIP ? (size_t)a.img : C * HW;
     const float *xb = a.in + (size_t)b * img;
     float *yb = a.out + (size_t)b * img;
     // weight fragments: Wf[(nt NGw + g) 64 + lane].e = K[co][ci][tap] for
@@ -2015,7 +2021,7 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int ci = 4 * cq + e;
-                const int at = (co * C + ci) * K2 + t;
+                const int at = FLIP ? (ci * C + co) * K2 + K2 - 1 - t : (co * C + ci) * K2 + t;
                 const int off = ok && ci < C ? at * 4 : (int)nrec;
                 v[h][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rk, off, 0, 0));
             }
@@ -2031,7 +2037,7 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
             const int t = fdiv(u, fp.d_ncq), cq = u - t * fp.ncq;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (t == selft && 4 * cq + e > co)
+                if (FLIP ? K2 - 1 - t == selft && co > 4 * cq + e : t == selft && 4 * cq + e > co)
                     v[h][e] = 0.0f;
             if (idx < nfrag)
                 Wf[idx] = make_float4(v[h][0], v[h][1], v[h][2], v[h][3]);
@@ -2176,7 +2182,8 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
         const int corner = fp.n == 1 ? corner0 : q;
         int oh, ow;
         self_tap(corner, K, oh, ow);
-        const int selft = oh * K + ow;
+        // (K's self tap; with FLIP its corner is the opposite of this launch's)
+        const int selft = FLIP ? (P - oh) * K + P - ow : oh * K + ow;
         if constexpr (ROWS) {
             if (q == 0)
                 __syncthreads();   // the fragments' zeros
@@ -2300,7 +2307,21 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
 template <bool PADW, bool ROWS, int MAXT>
 __global__ __launch_bounds__(MAXT) void forward_kernel(FwdArgs a) {
     extern __shared__ float sm[];
-    forward_block<PADW, ROWS>(a, blockIdx.x, sm);
+    forward_block<PADW, ROWS, false>(a, blockIdx.x, sm);
+}
+
+// The gradients of a layer: dK's blocks (none where it is not wanted), which take
+// longer, then dx's.  One launch, so that the latency-bound blocks of either fill
+// the other's gaps: 12 x 32 x 32, batch 64, with the parts' sum 20.1 us in two
+// launches, 15.3 in one (34.5 with dx as an implicit GEMM over K); 3 x 8 x 8 of
+// one image 8.9 and 5.2 (7.0).
+template <bool PADW, int KK>
+__global__ __launch_bounds__(kFwdThreads) void grad_kernel(FwdArgs a, DkArgs dk) {
+    extern __shared__ float sm[];
+    if ((int)blockIdx.x < dk.blocks)
+        dk_tile<KK, false>(dk, blockIdx.x, sm);
+    else
+        forward_block<PADW, false, true>(a, blockIdx.x - dk.blocks, sm);
 }
 
 bool valid_shape(int B, int C, int H, int W, int k) {
@@ -2924,6 +2945,48 @@ int scratch_of_device(void **out) {
 }
 
 }  // namespace
+
+// The gradients of one layer (arguments checked by the caller).
+int finc_detail::layer_grads(const float *dy, float *dx, const float *K, int B, int C, int H,
+                             int W, int k, int corner, long long img, const DkArgs &dk,
+                             hipStream_t stream) {
+    FwdArgs a;
+    memset(&a, 0, sizeof(a));
+    a.in = dy;
+    a.out = dx;
+    a.K = K;
+    a.img = img;
+    a.fp = make_fwd_plan(C, H, W, k, 1, 3 - corner, B, false);
+    a.nfwd = B * a.fp.nblk;
+    size_t lds = (size_t)a.fp.lds_floats * sizeof(float);
+    const void *fk = nullptr;
+    auto pick = [&](auto kc) {
+        constexpr int KK = decltype(kc)::value;
+        fk = a.fp.padw ? reinterpret_cast<const void *>(grad_kernel<true, KK>)
+                       : reinterpret_cast<const void *>(grad_kernel<false, KK>);
+        if (dk.blocks > 0 && lds < dk_lds_floats<KK>() * sizeof(float))
+            lds = dk_lds_floats<KK>() * sizeof(float);
+    };
+    switch (k) {
+    case 1: pick(std::integral_constant<int, 1>{}); break;
+    case 2: pick(std::integral_constant<int, 2>{}); break;
+    case 3: pick(std::integral_constant<int, 3>{}); break;
+    case 4: pick(std::integral_constant<int, 4>{}); break;
+    case 5: pick(std::integral_constant<int, 5>{}); break;
+    case 6: pick(std::integral_constant<int, 6>{}); break;
+    default: pick(std::integral_constant<int, 7>{}); break;
+    }
+    const int rc = check_lds(lds);
+    if (rc != FINC_OK)
+        return rc;
+    if (hipFuncSetAttribute(fk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        (void)hipGetLastError();   // not needed on every runtime; the launch check decides
+    DkArgs da = dk;
+    void *args[] = {&a, &da};
+    (void)hipLaunchKernel(fk, dim3((unsigned)(a.nfwd + dk.blocks)), dim3(kFwdThreads), args, lds,
+                          stream);
+    return launched();
+}
 
 // ===========================================================================
 // C ABI

@@ -68,6 +68,34 @@ def test_unit_backward(orc, shape):
     assert torch.equal(dx, dx2) and torch.equal(dK4, dK42)
 
 
+# The tiles of dK and of the launch that holds both gradients: one part (written
+# in place) and several, channel tiles of 1 / 15 / 16 / 17 / 33, every k (taps in
+# groups of nine from k = 3), rows wider than a band with a remainder of one
+# column, rows of one pixel, bands shorter than the image, and the input
+# gradient's other kernel (48 channels at k = 5: its weights outgrow LDS).
+GRAD_SHAPES = [(1, 1, 1, 1, 1), (1, 15, 3, 33, 3), (2, 16, 5, 65, 2), (3, 17, 33, 7, 4),
+               (2, 33, 9, 8, 3), (5, 3, 40, 1, 5), (1, 4, 11, 31, 6), (2, 5, 7, 64, 7),
+               (70, 2, 8, 8, 3), (2, 48, 6, 9, 5)]
+
+
+@pytest.mark.parametrize("corner", [0, 2, 3])
+@pytest.mark.parametrize("shape", GRAD_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_layer_gradient_tiles(orc, shape, corner):
+    B, C, H, W, k = shape
+    rng = np.random.default_rng(C * 10 + corner)
+    x, dy = rng.normal(size=(B, C, H, W)), rng.normal(size=(B, C, H, W))
+    K = synth.garbage_in_mask(synth.masked_kernel(C, k, corner, 40 + C), corner, seed=k)
+    print("layer backward", shape, corner, flush=True)
+    dx, dK = finc.backward(dev(x), dev(dy), dev(K), corner, -1.0, dx=poisoned(x.shape),
+                           dK=poisoned(K.shape))
+    want_dx, want_dK = orc.backward(f64(x), f64(dy), f64(K), corner, -1.0)
+    assert_close(host(dx), want_dx, f"dx {shape}")
+    _, sq = orc.backward(f64(x) ** 2, f64(dy) ** 2, f64(K), corner, 0.0)
+    assert_close(host(dK), want_dK, f"dK {shape}", scale=np.sqrt(sq))
+    assert torch.equal(finc.backward(dev(x), dev(dy), dev(K), corner, -1.0, want_dK=False)[0], dx)
+    assert torch.equal(finc.backward(dev(x), dev(dy), dev(K), corner, -1.0, want_dx=False)[1], dK)
+
+
 def test_unit_backward_workload(orc):
     """The unit workload's shape (256 images of 12 x 16 x 16, k = 3): dK4
     sums 65,536 pixels per tap; dx on three sampled images; dx alone and dK
