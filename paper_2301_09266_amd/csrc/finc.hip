@@ -48,7 +48,6 @@ using namespace finc_detail;
 namespace {
 
 constexpr int kWave = 64;
-constexpr int kPrepThreads = 64;
 constexpr int kMaxLayersPerPrep = 64;
 constexpr int kMaxLevels = 8;
 
@@ -171,7 +170,6 @@ struct PrepArgs {
 };
 
 constexpr int kPrepBlk = 16;             // unknowns solved in registers at a time
-constexpr int kPrepMax = 64;             // FINC_MAX_C rounded up to kPrepBlk
 
 __host__ __device__ inline int prep_cb(int C) { return (C + kPrepBlk - 1) / kPrepBlk * kPrepBlk; }
 
@@ -187,10 +185,10 @@ __host__ __device__ inline int prep_lds_doubles(int C, int nth) {
 // One block's share of one layer's preparation: output rows (columns of the
 // solves) col0 .. col0 + NTH - 1, row = (kernel position s, input channel
 // ci).  zero_tail: this block also writes the layer's zero block.
-template <int NTH>
+template <int NTH, int CB>   // CB = prep_cb(C)
 __device__ __forceinline__ void prep_columns(const float *__restrict__ K, float *out, int C, int k,
                                              int corner, int col0, bool zero_tail, double *lds) {
-    const int kk = k * k, CP = round_up4(C), CB = prep_cb(C), tid = threadIdx.x;
+    const int kk = k * k, CP = round_up4(C), tid = threadIdx.x;
     // Lt[c CB + m] = L[m][c] for m > c, else 0 (fp32: converting to fp64 is
     // exact, and a column's multipliers are read 16 bytes at a time)
     float *Lt = reinterpret_cast<float *>(lds);
@@ -216,49 +214,32 @@ __device__ __forceinline__ void prep_columns(const float *__restrict__ K, float 
         return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rk, off, 0, 0));
     };
     auto Kself = [&](int m, int c) { return kat(((m * C + c) * kk + ss) * 4); };
-    // Staging: every load of a round is issued before the round's stores, so
-    // a round costs one memory latency; the first round holds the first 16
-    // right-hand-side rows (kept in registers), U entries of L per thread and
-    // the diagonal (all of it for C <= 16).
-    constexpr int U = 8;
+    // Staging: every load -- all rows of the right-hand side (the first 16 stay
+    // in registers), this thread's entries of L and the diagonal -- is issued
+    // before the first store, so it costs one memory latency.
+    constexpr int U = (CB * CB + NTH - 1) / NTH;   // entries of L per thread
     const int rbase = real ? (ci * kk + ka * k + kb) * 4 : (int)nrec;   // rhs(m) at rbase + m ckk 4
     auto rhs = [&](int m) { return kat(rbase + m * ckk * 4); };
     auto rhs_val = [&](int m, float v) {
         return (m < C && real) ? (is_self ? (m == ci ? 1.0 : 0.0) : (double)v) : 0.0;
     };
-    // entry idx = c CB + m of L's staging (column c, row m), stepped by NTH
-    // from this thread's first one without a division per entry
-    const int dc = NTH / CB, dm = NTH - dc * CB;
-    int lc = tid / CB, lm = tid - lc * CB;
-    auto lstep = [&](int &c, int &m) {
-        c += dc;
-        m += dm;
-        if (m >= CB) {
-            m -= CB;
-            c += 1;
-        }
-    };
     auto put_l = [&](int c, int m, float v) {
         if (c < CB)
             Lt[c * CB + m] = (m > c && m < C) ? v : 0.0f;
     };
+    // (entry idx = c CB + m of L: column c, row m)
     double z[kPrepBlk];
     {
-        float rv[kPrepBlk], lv[U];
-        int cs[U], ms[U];
+        float rv[CB], lv[U];
 #pragma unroll
-        for (int u = 0; u < kPrepBlk; ++u)
+        for (int u = 0; u < CB; ++u)
             rv[u] = rhs(u);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            cs[u] = lc;
-            ms[u] = lm;
-            lv[u] = Kself(lm, lc);
-            lstep(lc, lm);
-        }
+        for (int u = 0; u < U; ++u)
+            lv[u] = Kself((tid + u * NTH) % CB, (tid + u * NTH) / CB);
         float dv = Kself(tid, tid);
 #pragma unroll
-        for (int u = 0; u < kPrepBlk; ++u)
+        for (int u = 0; u < CB; ++u)
             pin(rv[u]);
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -269,38 +250,12 @@ __device__ __forceinline__ void prep_columns(const float *__restrict__ K, float 
             z[u] = rhs_val(u, rv[u]);
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            put_l(cs[u], ms[u], lv[u]);
+            put_l((tid + u * NTH) / CB, (tid + u * NTH) % CB, lv[u]);
         if (tid < CB)
             rinv[tid] = tid < C ? 1.0 / (double)dv : 1.0;
-    }
-    while (lc < CB) {
-        float v[U];
-        int cs[U], ms[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            cs[u] = lc;
-            ms[u] = lm;
-            v[u] = Kself(lm, lc);
-            lstep(lc, lm);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            pin(v[u]);
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            put_l(cs[u], ms[u], v[u]);
-    }
-    for (int base = kPrepBlk; base < CB; base += kPrepBlk) {
-        float v[kPrepBlk];
-#pragma unroll
-        for (int u = 0; u < kPrepBlk; ++u)
-            v[u] = rhs(base + u);
-#pragma unroll
-        for (int u = 0; u < kPrepBlk; ++u)
-            pin(v[u]);
-#pragma unroll
-        for (int u = 0; u < kPrepBlk; ++u)
-            zs[(base + u - kPrepBlk) * NTH + tid] = rhs_val(base + u, v[u]);
+        for (int u = kPrepBlk; u < CB; ++u)
+            zs[(u - kPrepBlk) * NTH + tid] = rhs_val(u, rv[u]);
     }
     __syncthreads();
     // kernel position (ka, kb) is back-offset (|ka - sh|, |kb - sw|) in the
@@ -340,12 +295,24 @@ __device__ __forceinline__ void prep_columns(const float *__restrict__ K, float 
                 if (b0 + i < CP)
                     dst[4 * (b0 + i)] = (float)(sg * z[i]);
         }
-        for (int m = b0 + kPrepBlk; m < CB; ++m) {
-            double acc = zs[(m - kPrepBlk) * NTH + tid];
+        // (four rows at a time: four chains of FMAs, one 16-byte read of L)
+        for (int m = b0 + kPrepBlk; m < CB; m += 4) {
+            double *zm = zs + (m - kPrepBlk) * NTH + tid;
+            double acc[4];
 #pragma unroll
-            for (int c = 0; c < kPrepBlk; ++c)
-                acc -= (double)Lt[(b0 + c) * CB + m] * z[c];
-            zs[(m - kPrepBlk) * NTH + tid] = acc;
+            for (int j = 0; j < 4; ++j)
+                acc[j] = zm[j * NTH];
+#pragma unroll
+            for (int c = 0; c < kPrepBlk; ++c) {
+                const float4 l = *reinterpret_cast<const float4 *>(Lt + (b0 + c) * CB + m);
+                acc[0] -= (double)l.x * z[c];
+                acc[1] -= (double)l.y * z[c];
+                acc[2] -= (double)l.z * z[c];
+                acc[3] -= (double)l.w * z[c];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                zm[j * NTH] = acc[j];
         }
     }
     if (zero_tail && tid < 16)
@@ -354,17 +321,18 @@ __device__ __forceinline__ void prep_columns(const float *__restrict__ K, float 
 }
 
 #if FINC_PART < 0
-__global__ __launch_bounds__(kPrepThreads) void prep_kernel(PrepArgs a) {
-    __shared__ double lds[kPrepMax * kPrepMax + kPrepMax + (kPrepMax - kPrepBlk) * kPrepThreads];
+template <int NTH, int CB>
+__global__ __launch_bounds__(NTH) void prep_kernel(PrepArgs a) {
+    extern __shared__ double prep_lds[];
     const int layer = blockIdx.y;
     const unsigned int cw = layer < 16   ? a.corner_bits[0]
                             : layer < 32 ? a.corner_bits[1]
                             : layer < 48 ? a.corner_bits[2]
                                          : a.corner_bits[3];
-    prep_columns<kPrepThreads>(a.K + (size_t)layer * a.C * a.C * a.k * a.k,
+    prep_columns<NTH, CB>(a.K + (size_t)layer * a.C * a.C * a.k * a.k,
                                a.out + (size_t)layer * prep_layer_floats(a.C, a.k), a.C, a.k,
-                               (cw >> (2 * (layer & 15))) & 3, blockIdx.x * kPrepThreads,
-                               blockIdx.x == 0, lds);
+                               (cw >> (2 * (layer & 15))) & 3, blockIdx.x * NTH,
+                               blockIdx.x == 0, prep_lds);
 }
 #endif
 
@@ -1947,7 +1915,7 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
         // (dispatched first: their latency chain is the longest; the forward
         // blocks do not wait for them)
         const int pb = block, layer = pb / a.ppl, part = pb - layer * a.ppl;
-        prep_columns<kFwdThreads>(a.K + (size_t)layer * fp.C * fp.C * fp.K * fp.K,
+        prep_columns<kFwdThreads, kPrepBlk>(a.K + (size_t)layer * fp.C * fp.C * fp.K * fp.K,
                                   a.prepared + (size_t)layer * prep_layer_floats(fp.C, fp.K),
                                   fp.C, fp.K, nprep == 1 ? fp.corner0 : layer, part * kFwdThreads,
                                   part == 0, reinterpret_cast<double *>(sm));
@@ -2499,8 +2467,25 @@ int launch_prep(const float *K, int n, const int *corners, int C, int k, float *
         a.out = out + (size_t)first * prep_layer_floats(C, k);
         for (int q = 0; q < a.n; ++q)
             a.corner_bits[q >> 4] |= (unsigned)(corners[first + q] & 3) << (2 * (q & 15));
-        dim3 grid((k * k * CP + kPrepThreads - 1) / kPrepThreads, a.n);
-        hipLaunchKernelGGL(prep_kernel, grid, dim3(kPrepThreads), 0, stream, a);
+        // one wave a block up to 16 channels (12: 4.4 us, with four 4.8), else four,
+        // which share L and its staging (48, four layers: 20.4 -> 16.1 us)
+        auto go = [&](auto nth, auto cb) {
+            constexpr int NTH = decltype(nth)::value, CB = decltype(cb)::value;
+            const size_t lds = prep_lds_doubles(C, NTH) * sizeof(double);
+            const void *fk = reinterpret_cast<const void *>(prep_kernel<NTH, CB>);
+            if (hipFuncSetAttribute(fk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+                hipSuccess)
+                (void)hipGetLastError();   // not needed on every runtime; the launch check decides
+            hipLaunchKernelGGL((prep_kernel<NTH, CB>), dim3(ceil_div(k * k * CP, NTH), a.n),
+                               dim3(NTH), lds, stream, a);
+        };
+        using std::integral_constant;
+        switch (prep_cb(C)) {
+        case 16: go(integral_constant<int, 64>{}, integral_constant<int, 16>{}); break;
+        case 32: go(integral_constant<int, 256>{}, integral_constant<int, 32>{}); break;
+        case 48: go(integral_constant<int, 256>{}, integral_constant<int, 48>{}); break;
+        default: go(integral_constant<int, 256>{}, integral_constant<int, 64>{}); break;
+        }
         const int rc = launched();
         if (rc != FINC_OK)
             return rc;
