@@ -272,6 +272,11 @@ __device__ __forceinline__ void prep_columns(const float *__restrict__ K, float 
         }
 #pragma unroll
         for (int c = 0; c < kPrepBlk; ++c) {
+            // (one block of channels beside the forward: without this the whole
+            // of L is read ahead, 177 registers, and the forward's blocks lose
+            // half of their waves)
+            if constexpr (CB == kPrepBlk && NTH > 64)
+                __builtin_amdgcn_sched_barrier(0);
             z[c] *= rinv[b0 + c];
             // column c's multipliers of rows b0 .. b0 + 15 (16-byte aligned:
             // CB and b0 are multiples of 16), read ahead of their use
@@ -1905,12 +1910,13 @@ constexpr int kFwdMinBlocks = 256;   // a block per compute unit of the chip
 // FLIP (one layer): K read transposed over channels and reversed in space,
 // K'[n][m][t] = K[m][n][k^2 - 1 - t], with K's masked entries zero: the layer's
 // input gradient is the forward of K' with the opposite corner.
-template <bool PADW, bool ROWS, bool FLIP>
+// PREP: the launch's first blocks may prepare weights.
+template <bool PADW, bool ROWS, bool FLIP, bool PREP>
 __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block, float *sm) {
     const FwdPlan &fp = a.fp;
     const int nprep = a.split ? 4 : fp.n;   // layers prepared
-    const int npre = a.prepared ? nprep * a.ppl : 0;
-    if (block < npre) {
+    const int npre = PREP && a.prepared ? nprep * a.ppl : 0;
+    if (PREP && block < npre) {
         // the weights for the inverse, prepared by the launch's first blocks
         // (dispatched first: their latency chain is the longest; the forward
         // blocks do not wait for them)
@@ -1922,7 +1928,7 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
         return;
     }
     const int C = fp.C, CP = fp.CP, H = fp.H, W = fp.W, K = fp.K, P = fp.P, WP = fp.WP;
-    if (a.logdet && block == npre) {
+    if (!FLIP && a.logdet && block == npre) {
         // log|det| on a block of its own (next after the preparation blocks,
         // so it is dispatched early and no forward block carries its fp64
         // logarithms): H W times the sum over the layers (or the four
@@ -1949,7 +1955,7 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
     const int lane = threadIdx.x & 63, kq = lane >> 4, li = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nwaves = blockDim.x >> 6;
-    const int bid = block - npre - (a.logdet ? 1 : 0);
+    const int bid = block - npre - (!FLIP && a.logdet ? 1 : 0);
     const int b = bid / fp.nblk, blk = bid - b * fp.nblk;
     const int corner0 = a.split ? (b & 3) : fp.corner0;   // this block's (first) corner
     const float *Kb = a.K + (a.split ? (size_t)(b & 3) * fp.C * fp.C * fp.K * fp.K : 0);
@@ -2275,7 +2281,7 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
 template <bool PADW, bool ROWS, int MAXT>
 __global__ __launch_bounds__(MAXT) void forward_kernel(FwdArgs a) {
     extern __shared__ float sm[];
-    forward_block<PADW, ROWS, false>(a, blockIdx.x, sm);
+    forward_block<PADW, ROWS, false, MAXT == kFwdThreads>(a, blockIdx.x, sm);
 }
 
 // The gradients of a layer: dK's blocks (none where it is not wanted), which take
@@ -2289,7 +2295,7 @@ __global__ __launch_bounds__(kFwdThreads) void grad_kernel(FwdArgs a, DkArgs dk)
     if ((int)blockIdx.x < dk.blocks)
         dk_tile<KK, false>(dk, blockIdx.x, sm);
     else
-        forward_block<PADW, false, true>(a, blockIdx.x - dk.blocks, sm);
+        forward_block<PADW, false, true, false>(a, blockIdx.x - dk.blocks, sm);
 }
 
 bool valid_shape(int B, int C, int H, int W, int k) {
