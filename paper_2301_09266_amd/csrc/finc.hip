@@ -264,6 +264,14 @@ __device__ __forceinline__ void prep_columns(const float *__restrict__ K, float 
     const double sg = is_self ? 1.0 : -1.0;
     const int t = tap_index(ka > sh ? ka - sh : sh - ka, kb > sw ? kb - sw : sw - kb, k);
     float *dst = out + ((size_t)(t * (CP / 4) + (ci >> 2)) * CP) * 4 + (ci & 3);
+    // Beside the forward (one block of channels, 256 threads) a column's step
+    // stays where it is written: its results pinned, so that the arithmetic
+    // cannot sink into the store's branch while all of L's reads stay ahead of
+    // it, and its reads kept behind the step before.  Otherwise the whole of L
+    // is live at once and sets the registers of the launch: 189 + 16, two waves
+    // a SIMD, against the forward's own 81 + 16, four (12 x 32 x 32, k = 5, batch
+    // 64, forward and inverse: 66.3 -> 64.2 us).
+    constexpr bool kSteps = CB == kPrepBlk && NTH > 64;
     for (int b0 = 0; b0 < CB; b0 += kPrepBlk) {
         if (b0 > 0) {
 #pragma unroll
@@ -272,10 +280,7 @@ __device__ __forceinline__ void prep_columns(const float *__restrict__ K, float 
         }
 #pragma unroll
         for (int c = 0; c < kPrepBlk; ++c) {
-            // (one block of channels beside the forward: without this the whole
-            // of L is read ahead, 177 registers, and the forward's blocks lose
-            // half of their waves)
-            if constexpr (CB == kPrepBlk && NTH > 64)
+            if constexpr (kSteps)
                 __builtin_amdgcn_sched_barrier(0);
             z[c] *= rinv[b0 + c];
             // column c's multipliers of rows b0 .. b0 + 15 (16-byte aligned:
@@ -293,6 +298,11 @@ __device__ __forceinline__ void prep_columns(const float *__restrict__ K, float 
 #pragma unroll
             for (int m = c + 1; m < kPrepBlk; ++m)
                 z[m] -= (double)lv[m] * z[c];
+            if constexpr (kSteps) {
+#pragma unroll
+                for (int m = c; m < kPrepBlk; ++m)
+                    pin(z[m]);
+            }
         }
         if (row_ok) {
 #pragma unroll
@@ -1910,7 +1920,8 @@ constexpr int kFwdMinBlocks = 256;   // a block per compute unit of the chip
 // FLIP (one layer): K read transposed over channels and reversed in space,
 // K'[n][m][t] = K[m][n][k^2 - 1 - t], with K's masked entries zero: the layer's
 // input gradient is the forward of K' with the opposite corner.
-// PREP: the launch's first blocks may prepare weights.
+// PREP: the launch's first blocks may prepare weights (up to kFusedPrepMaxC
+// channels, one tile: never with ROWS).
 template <bool PADW, bool ROWS, bool FLIP, bool PREP>
 __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block, float *sm) {
     const FwdPlan &fp = a.fp;
@@ -2281,7 +2292,7 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
 template <bool PADW, bool ROWS, int MAXT>
 __global__ __launch_bounds__(MAXT) void forward_kernel(FwdArgs a) {
     extern __shared__ float sm[];
-    forward_block<PADW, ROWS, false, MAXT == kFwdThreads>(a, blockIdx.x, sm);
+    forward_block<PADW, ROWS, false, MAXT == kFwdThreads && !ROWS>(a, blockIdx.x, sm);
 }
 
 // The gradients of a layer: dK's blocks (none where it is not wanted), which take
