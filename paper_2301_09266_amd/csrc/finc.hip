@@ -2355,7 +2355,9 @@ int plan_inverse(InvArgs &a, size_t *lds_bytes, int *threads) {
 // blocks of rows (up to eight 16-pixel tiles a block, and a block per compute
 // unit when the batch allows); a unit (n = 4) keeps whole images.
 // whole: a unit keeps whole images (in place: an image must be read whole
-// before any of it is written).
+// before any of it is written).  lds_floats is above kLdsBytes where no block
+// of rows fits; the rest of the plan is then unset.
+constexpr long long kNoFitFloats = (1ll << 29) - 1;   // (as bytes still an int)
 FwdPlan make_fwd_plan(int C, int H, int W, int K, int n, int corner0, int B, bool whole) {
     FwdPlan p;
     memset(&p, 0, sizeof(p));
@@ -2398,32 +2400,43 @@ FwdPlan make_fwd_plan(int C, int H, int W, int K, int n, int corner0, int B, boo
             p.RB = imax(rb_min, p.RB / 2);
     }
     // LDS layout for the rows of a block; blocks (bands, for a unit not
-    // computed in place) are halved further while it does not fit
+    // computed in place) are halved further while it does not fit.  The sizes
+    // are 64-bit: a wide row's would wrap, and a layout is narrowed only once
+    // it fits.
+    constexpr long long limit = kLdsBytes / sizeof(float);
+    long long in = 0, out = 0, wts = 0, need = 0;
     auto layout = [&] {
         p.nblk = ceil_div(H, p.RB);
         p.HB = n > 1 && p.nblk > 1 ? 2 * p.P : p.P;
-        p.offI = 0;
-        p.offO = (p.RB + 2 * p.HB) * p.WP * p.CP;
-        p.offW = p.offO + (n > 1 ? imin(H, p.RB + 3 * p.P) * W * p.CP : 0);
         p.NGw = p.padw ? p.NG : p.NGr;
-        p.offD = p.offW + (p.NT * p.NGw + (p.padw ? 0 : 1)) * 256;   // (+ the zero fragment)
-        p.lds_floats = p.offD + round_up4(4 * p.NG);
+        in = (long long)(p.RB + 2 * p.HB) * p.WP * p.CP;
+        out = n > 1 ? (long long)imin(H, p.RB + 3 * p.P) * W * p.CP : 0;
+        wts = (long long)(p.NT * p.NGw + (p.padw ? 0 : 1)) * 256;   // (+ the zero fragment)
+        need = in + out + wts + round_up4(4 * p.NG);
     };
     const int rb0 = p.RB;
     auto fit = [&] {
         p.RB = rb0;
         layout();
-        while ((size_t)p.lds_floats * sizeof(float) > kLdsBytes && p.RB > rb_min &&
-               !(n > 1 && whole)) {
+        while (need > limit && p.RB > rb_min && !(n > 1 && whole)) {
             p.RB = imax(rb_min, p.RB / 2);
             layout();
         }
     };
     fit();
-    if ((size_t)p.lds_floats * sizeof(float) > kLdsBytes && p.NG > p.NGr) {
+    if (need > limit && p.NG > p.NGr) {
         p.padw = 0;   // the padding groups' fragments do not fit: one zero fragment
         fit();
     }
+    if (need > limit) {   // refused by every caller: more LDS than any device has
+        p.lds_floats = (int)(need < kNoFitFloats ? need : kNoFitFloats);
+        return p;
+    }
+    p.offI = 0;
+    p.offO = (int)in;
+    p.offW = (int)(in + out);
+    p.offD = (int)(in + out + wts);
+    p.lds_floats = (int)need;
     const int rb_last = H - (p.nblk - 1) * p.RB;
     p.d_plane = make_fastdiv((p.RB + 2 * p.HB) * p.WP);
     p.d_plane_last = make_fastdiv((rb_last + 2 * p.HB) * p.WP);
@@ -2958,6 +2971,8 @@ int finc_detail::layer_grads(const float *dy, float *dx, const float *K, int B, 
     a.out = dx;
     a.K = K;
     a.img = img;
+    if (!valid_shape(B, C, H, W, k))   // (the forward's bound on H W, which the caller has not)
+        return FINC_EUNSUPPORTED;
     a.fp = make_fwd_plan(C, H, W, k, 1, 3 - corner, B, false);
     a.nfwd = B * a.fp.nblk;
     size_t lds = (size_t)a.fp.lds_floats * sizeof(float);

@@ -1,0 +1,71 @@
+"""What the built library launches, without a GPU (tests/launch_drive.cpp stands
+in for the HIP runtime): which kernel a shape takes, and that its grid, block
+and LDS are within the device's limits."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2301_09266_amd import finc
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+LDS = 160 * 1024
+
+
+@pytest.fixture(scope="module")
+def drive(tmp_path_factory):
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not found")
+    exe = str(tmp_path_factory.mktemp("drive") / "launch_drive")
+    subprocess.run([HIPCC, "--offload-host-only", "-x", "c++", "-std=c++17", "-O1", "-rdynamic",
+                    "-I", os.path.join(ROOT, "include"), "-I", "/opt/rocm/include",
+                    "-D__HIP_PLATFORM_AMD__", os.path.join(ROOT, "tests", "launch_drive.cpp"),
+                    "-ldl", "-o", exe], check=True)
+
+    def run(calls):
+        """[(op, want, B, C, H, W, k, corner)] -> [(rc, [(kernel, blocks, threads, lds)])]"""
+        text = "".join(" ".join(map(str, c)) + "\n" for c in calls)
+        r = subprocess.run([exe, finc.LIB_PATH], input=text, capture_output=True, text=True,
+                           timeout=120)
+        assert r.returncode == 0, r.stderr
+        out = []
+        for line in r.stdout.splitlines():
+            rc, *ls = line.split(";")
+            out.append((int(rc), [(n, int(b), int(t), int(s)) for n, b, t, s in
+                                  (x.rsplit(",", 3) for x in ls)]))
+        assert len(out) == len(calls)
+        return out
+    return run
+
+
+def names(launches):
+    return ["gemm" if "gemm_grad_kernel" in n else "fwd" if "11grad_kernel" in n else
+            "dk" if "9dk_kernel" in n else "sum" if "dk_reduce" in n else n
+            for n, _, _, _ in launches]
+
+
+# rows so wide that the row block's LDS size passes 2^32 floats and more, where
+# a 32-bit size would come out small: (C, k, width), one row of one image
+WIDE = [(20, 7, 16519032), (20, 7, 16519126), (52, 3, 16519100)] + [
+    (C, k, W) for C, k in ((20, 7), (52, 3), (64, 7), (33, 5), (64, 2))
+    for m in (1, 2) for cp in [(C + 3) // 4 * 4]
+    for W in range(max(1, m * 2**32 // ((1 + 2 * (k - 1)) * cp) - 160),
+                   m * 2**32 // ((1 + 2 * (k - 1)) * cp) + 8, 7) if W < 2**24]
+
+
+def test_wide_rows_are_refused():
+    for C, k, W in WIDE:
+        for kind in (finc.PLAN_LAYER, finc.PLAN_UNIT):
+            assert finc.forward_plan(kind, 1, C, 1, W, k) == finc.EUNSUPPORTED, (kind, C, k, W)
+
+
+def test_backward_of_wide_rows_is_a_gemm(drive):
+    """Where the forward's row blocks do not fit, dx is the implicit GEMM: also
+    past the forward's own bound of 2^24 pixels an image."""
+    shapes = [(1, C, 1, W, k) for C, k, W in WIDE]
+    shapes += [(1, 1, 1, 82595513, 7), (1, 1, 1, 214748361, 3), (1, 2, 3, 1 << 24, 3)]
+    for s, (rc, ls) in zip(shapes, drive([("backward", 1, *s, 0) for s in shapes])):
+        assert rc == finc.OK and names(ls) == ["gemm"], (s, rc, ls)
+    rc, ls = drive([("backward", 1, 64, 12, 32, 32, 3, 0)])[0]
+    assert rc == finc.OK and names(ls) == ["fwd"]
