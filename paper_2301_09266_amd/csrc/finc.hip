@@ -1915,6 +1915,7 @@ struct FwdArgs {
 constexpr int kFwdThreads = 256;       // (preparation blocks and single layers)
 constexpr int kFwdUnitThreads = 512;
 constexpr int kFwdMinBlocks = 256;   // a block per compute unit of the chip
+constexpr long long kMaxGridThreads = (1ll << 32) - 1;
 
 // ROWS: how the weights reach LDS (units of several channel tiles; see below).
 // FLIP (one layer): K read transposed over channels and reversed in space,
@@ -2974,6 +2975,9 @@ int finc_detail::layer_grads(const float *dy, float *dx, const float *K, int B, 
     if (!valid_shape(B, C, H, W, k))   // (the forward's bound on H W, which the caller has not)
         return FINC_EUNSUPPORTED;
     a.fp = make_fwd_plan(C, H, W, k, 1, 3 - corner, B, false);
+    // (a launch of 2^32 threads or more is refused: each image is a block here)
+    if ((long long)B * a.fp.nblk + dk.blocks > kMaxGridThreads / kFwdThreads)
+        return FINC_EUNSUPPORTED;
     a.nfwd = B * a.fp.nblk;
     size_t lds = (size_t)a.fp.lds_floats * sizeof(float);
     const void *fk = nullptr;

@@ -69,3 +69,16 @@ def test_backward_of_wide_rows_is_a_gemm(drive):
         assert rc == finc.OK and names(ls) == ["gemm"], (s, rc, ls)
     rc, ls = drive([("backward", 1, 64, 12, 32, 32, 3, 0)])[0]
     assert rc == finc.OK and names(ls) == ["fwd"]
+
+
+@pytest.mark.parametrize("want", [1, 2, 3])
+def test_backward_grids(drive, want):
+    """Every launch of the backward is one the device takes: under 2^32 threads
+    (2^24 images of a pixel included), LDS of a workgroup, no empty grid."""
+    shapes = [(1 << 24, 1, 2, 2, 3), ((1 << 24) - 1, 1, 1, 1, 3), (1 << 26, 4, 1, 1, 1),
+              (1 << 20, 3, 2, 2, 3), (1, 1, 1, 1, 1), (64, 48, 8, 8, 3), (2, 64, 40, 40, 7),
+              (33, 23, 27, 19, 5), (1, 12, (1 << 24) + 5, 1, 2), (1, 1, (1 << 31) - 130, 1, 1)]
+    for s, (rc, ls) in zip(shapes, drive([("backward", want, *s, 3) for s in shapes])):
+        assert rc == finc.OK and ls, (s, rc, ls)
+        for n, blocks, threads, lds in ls:
+            assert 0 < blocks * threads < 2**32 and lds <= LDS, (s, n, blocks, threads, lds)
