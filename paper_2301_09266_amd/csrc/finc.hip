@@ -422,6 +422,8 @@ __global__ __launch_bounds__(kWave) void logdet_kernel(const float *K, int n, in
 // ---------------------------------------------------------------------------
 constexpr int kMaxWaves = 16;
 constexpr size_t kLdsBytes = 160 * 1024;   // LDS of a gfx950 workgroup
+// LDS floats of a plan that fits no device (as bytes still an int)
+constexpr long long kNoFitFloats = 1ll << 28;
 constexpr int kMaxGroups = 8;                       // quad groups (x4 quads) per wave
 // critical-wave forms an inverse instance is built with (low two bits of
 // its MODE), and kOneLayer: a single level of a single layer without actnorm
@@ -529,8 +531,11 @@ inline bool make_plan(int C, int H, int W, int K, Plan &p, bool stream = false) 
         p.offY = (H + p.P) * kRing * p.CP;
         p.offR = p.offY + H * kRing * p.CP;
     } else {
-        p.offY = (H + 2 * p.P) * p.WP * p.CP;
-        p.offR = p.offY + H * W * p.CP;
+        // (a wide row's sizes do not wrap: at kNoFitFloats the level fits nowhere)
+        const long long x = (long long)(H + 2 * p.P) * p.WP * p.CP;
+        const long long y = x + (long long)H * W * p.CP;
+        p.offY = (int)(x < kNoFitFloats ? x : kNoFitFloats);
+        p.offR = (int)(y < kNoFitFloats ? y : kNoFitFloats);
     }
     for (p.compact = 0; p.compact < 2; ++p.compact) {
         p.RS = p.compact ? p.S : p.S4;
@@ -2342,7 +2347,8 @@ int plan_inverse(InvArgs &a, size_t *lds_bytes, int *threads) {
         // overlap
         if (l > 0) {
             const Plan &u = a.lv[l - 1].pl;
-            const int last = u.offX + ((u.H - 1 + u.P) * u.WP + u.W - 1 + u.P) * u.CP + u.CP - 1;
+            const long long last =
+                u.offX + ((long long)(u.H - 1 + u.P) * u.WP + u.W - 1 + u.P) * u.CP + u.CP - 1;
             if (last >= p.offY)
                 return FINC_EUNSUPPORTED;
         }
@@ -2358,7 +2364,6 @@ int plan_inverse(InvArgs &a, size_t *lds_bytes, int *threads) {
 // whole: a unit keeps whole images (in place: an image must be read whole
 // before any of it is written).  lds_floats is above kLdsBytes where no block
 // of rows fits; the rest of the plan is then unset.
-constexpr long long kNoFitFloats = (1ll << 29) - 1;   // (as bytes still an int)
 FwdPlan make_fwd_plan(int C, int H, int W, int K, int n, int corner0, int B, bool whole) {
     FwdPlan p;
     memset(&p, 0, sizeof(p));

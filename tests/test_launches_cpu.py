@@ -60,6 +60,23 @@ def test_wide_rows_are_refused():
             assert finc.forward_plan(kind, 1, C, 1, W, k) == finc.EUNSUPPORTED, (kind, C, k, W)
 
 
+def test_inverse_of_wide_rows_is_streamed_or_refused():
+    """Such an image is not held in LDS: up to 16 channels the stream form takes
+    the layer, else it is refused."""
+    for C, k, H in ((48, 3, 1), (5, 3, 2), (12, 7, 1), (20, 5, 2), (64, 2, 1), (33, 7, 16)):
+        cp, P = (C + 3) // 4 * 4, k - 1
+        for m in (1, 2, 3):   # the layout's sizes just past m 2^32 floats
+            last = (m * 2**32 - (H + 2 * P) * 2 * P * cp) // ((2 * H + 2 * P) * cp)
+            for W in range(last - 40, last + 400, 9):
+                if not 0 < W * H < 2**24:
+                    continue
+                p = finc.inverse_plan(finc.PLAN_LAYER, C, H, W, k)
+                if C <= 16:
+                    assert p[0]["streamed"], (C, k, H, W)
+                else:
+                    assert p == finc.EUNSUPPORTED, (C, k, H, W, p)
+
+
 def test_backward_of_wide_rows_is_a_gemm(drive):
     """Where the forward's row blocks do not fit, dx is the implicit GEMM: also
     past the forward's own bound of 2^24 pixels an image."""
