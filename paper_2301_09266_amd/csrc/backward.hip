@@ -37,10 +37,10 @@ inline bool overlapb(const void *a, size_t na, const void *b, size_t nb) {
 }
 
 // dK's blocks alone (dK without dx, and images of 2 GB or more).
-template <int K, bool BIG>
+template <int K, int FORM, bool BIG>
 __global__ __launch_bounds__(256) void dk_kernel(DkArgs a) {
-    __shared__ __attribute__((aligned(16))) float lds[dk_lds_floats<K>()];
-    dk_tile<K, BIG>(a, blockIdx.x, lds);
+    __shared__ __attribute__((aligned(16))) float lds[dk_lds_floats<K, FORM>()];
+    dk_tile<K, FORM, BIG>(a, blockIdx.x, lds);
 }
 
 // dK = the sum of the parts, in a fixed order: of the eight groups of 32 threads
@@ -75,9 +75,11 @@ __global__ __launch_bounds__(256) void dk_reduce_kernel(const float *partial, in
     dK[e] = dk_entry(v, co, ci, t, K, gld, C, k, H, W, oh, ow);
 }
 
-// Parts of the position reduction: at least 2 chunks of 64 positions each,
-// about 512 blocks over the chip (two per CU), and at most 16 M floats of
-// partial sums.
+// The most parts of the position reduction, whose sums the workspace holds: of
+// 128 positions and more each, 512 for each 64 columns of C k^2 and 16 rows of C
+// together, and at most 16 M floats of partial sums.  (A part has nt^2 blocks for
+// each nine taps, fewer than that for several channel tiles: 48 x 8 x 8, batch
+// 64 runs 198.)
 int dk_parts(int B, int C, int H, int W, int k) {
     const long long nchunk = ((long long)B * H * W + 63) / 64;
     const long long tiles = (long long)((C * k * k + 63) / 64) * ((C + 15) / 16);
@@ -88,6 +90,61 @@ int dk_parts(int B, int C, int H, int W, int k) {
     if (parts > cap)
         parts = cap;
     return (int)(parts < 1 ? 1 : parts);
+}
+
+// dK's bands: 32 columns (more where there are less than eight rows), and rows,
+// or whole images, up to kDkPos positions and dk_x pixels with the halo; of
+// these, cut from the most, the ones that take the blocks (tiles of them a part,
+// `most` parts) the least time.  A band's time is that of its positions, while
+// every compute unit has a block or less however few blocks there are, of the
+// pixels it stages, about a third of a position each, and of its latencies, about
+// 64 positions; a cut has to gain 15%.  us, dK alone, one image a band of whole
+// rows -> these: 12 x 4 x 4, batch 96 16.0 -> 9.6; 12 x 16 x 16, batch 64 10.5 ->
+// 9.3; 12 x 2 x 2, batch 4096 46 -> 12; 12 x 1 x 1, batch 4096 175 -> 11.
+void dk_bands(DkArgs &a, int B, int H, int W, int k, bool big, int tiles, int most) {
+    // (rows of more than a band: the halo that cropping saves is not worth it)
+    const bool crop = !big && W <= 32;
+    a.pr = H < k && crop ? H - 1 : k - 1;
+    a.pc = W < k && crop ? W - 1 : k - 1;
+    int wb = 32;
+    if (H < kDkPos / wb) {
+        const int x = dk_x(k, false) / (H + a.pr) - a.pc;
+        wb = kDkPos / H < x ? kDkPos / H : x;
+    }
+    if (wb > W)
+        wb = W;
+    const int rows = dk_x(k, false) / (wb + a.pc) - a.pr;
+    int rb = kDkPos / wb < rows ? kDkPos / wb : rows, ni = 1;
+    if (rb >= H) {
+        rb = H;
+        const int x = dk_x(k, true) / ((H + a.pr) * (W + a.pc));
+        if (wb == W && x > 1)
+            ni = kDkPos / (H * W) < x ? kDkPos / (H * W) : x;
+    }
+    double best = 0.0;
+    for (;;) {
+        const long long nb = (long long)cdiv(B, ni) * cdiv(H, rb) * cdiv(W, wb);
+        const long long bpp = (nb + most - 1) / most, blocks = (nb + bpp - 1) / bpp * tiles;
+        const double pos = (double)ni * rb * wb, x = (double)ni * (rb + a.pr) * (wb + a.pc);
+        const double t = bpp * (64.0 + pos * (blocks > 256 ? blocks / 256.0 : 1.0) + 0.3 * x);
+        if (best == 0.0 || t < 0.85 * best) {
+            best = t;
+            a.ni = ni;
+            a.RB = rb;
+            a.WB = wb;
+        }
+        const int each = cdiv(B, most);   // images of a part
+        if (ni > 1)
+            ni = ni > each ? each : (ni + 1) / 2;
+        else if (rb > 1)
+            rb = (rb + 1) / 2;
+        else if (wb > 32)
+            wb = wb > 64 ? (wb + 1) / 2 : 32;
+        else
+            break;
+    }
+    a.bx = cdiv(W, a.WB);
+    a.form = a.pr < k - 1 || a.pc < k - 1 ? kDkCrop : a.ni > 1 ? kDkMulti : kDkOne;
 }
 
 bool valid_bwd_shape(int B, int C, int H, int W, int k) {
@@ -101,12 +158,12 @@ bool valid_bwd_shape(int B, int C, int H, int W, int k) {
 // conv_gemm.h on K read transposed and flipped, beside dK's blocks (da.blocks of
 // them, or none).  dx in tiles of 64 c_out x 64 pixels at 64 channels, else
 // 16 x 128, or 16 x 64 while there are fewer than two blocks a compute unit.
-template <int R, int WCO, int NS>
+template <int R, int WCO, int NS, int FORM>
 __global__ __launch_bounds__(256) void gemm_grad_kernel(ConvArgs ca, int gx, DkArgs da) {
-    constexpr int nc = conv_lds_floats<WCO, NS>(), nd = dk_lds_floats<R>();
+    constexpr int nc = conv_lds_floats<WCO, NS>(), nd = dk_lds_floats<R, FORM>();
     __shared__ __attribute__((aligned(16))) float lds[nc > nd ? nc : nd];
     if ((int)blockIdx.x < da.blocks) {
-        dk_tile<R, false>(da, blockIdx.x, lds);
+        dk_tile<R, FORM, false>(da, blockIdx.x, lds);
         return;
     }
     const int b = blockIdx.x - da.blocks;
@@ -119,8 +176,10 @@ void launch_gemm_grad(const ConvArgs &a, const DkArgs &da, hipStream_t st) {
     auto go = [&](auto wco, auto ns) {
         constexpr int WCO = decltype(wco)::value, NS = decltype(ns)::value;
         const int gx = cdiv(Q, 16 * NS * (4 / WCO)), g = gx * cdiv(a.Co, 16 * WCO);
-        hipLaunchKernelGGL((gemm_grad_kernel<R, WCO, NS>), dim3(da.blocks + g), dim3(kConvThreads),
-                           0, st, a, gx, da);
+        auto *kernel = da.form == kDkCrop    ? gemm_grad_kernel<R, WCO, NS, kDkCrop>
+                       : da.form == kDkMulti ? gemm_grad_kernel<R, WCO, NS, kDkMulti>
+                                             : gemm_grad_kernel<R, WCO, NS, kDkOne>;
+        hipLaunchKernelGGL(kernel, dim3(da.blocks + g), dim3(kConvThreads), 0, st, a, gx, da);
     };
     if (a.Co >= 64 && cdiv(Q, 64) >= 256)
         go(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
@@ -154,6 +213,7 @@ int launch_layer_backward(const float *x, const float *dy, const float *K, float
     const int oh = (corner == FINC_TL || corner == FINC_TR) ? k - 1 : 0;
     const int ow = (corner == FINC_TL || corner == FINC_BL) ? k - 1 : 0;
     const int n = C * C * k * k;
+    const bool big = (long long)C * H * W * 4 >= (1ll << 31);
     // dK, in partial sums over parts of the positions
     int parts = 0;
     DkArgs da;
@@ -171,22 +231,13 @@ int launch_layer_backward(const float *x, const float *dy, const float *K, float
         da.oh = oh;
         da.ow = ow;
         da.N = C * k * k;
+        da.B = B;
         da.nt = cdiv(C, 16);
-        const int groups = cdiv(k * k, dk_taps(k));
-        // bands of up to 256 positions, cut, to no less than 64, while there are
-        // fewer blocks than compute units
-        da.WB = W < 32 ? W : 32;
-        da.bx = cdiv(W, da.WB);
-        da.RB = kDkPos / da.WB < 32 ? kDkPos / da.WB : 32;
-        if (da.RB > H)
-            da.RB = H;
-        while (da.RB > 1 && da.RB * da.WB > 64 &&
-               (long long)B * cdiv(H, da.RB) * da.bx * da.nt * da.nt * groups < 256)
-            da.RB = (da.RB + 1) / 2;
+        const int groups = cdiv(k * k, dk_taps(k)), most = dk_parts(B, C, H, W, k);
+        dk_bands(da, B, H, W, k, big, da.nt * da.nt * groups, most);
         da.nbi = cdiv(H, da.RB) * da.bx;
-        da.nb = B * da.nbi;
-        parts = dk_parts(B, C, H, W, k);
-        da.bpp = cdiv(da.nb, parts);
+        da.nb = cdiv(B, da.ni) * da.nbi;
+        da.bpp = cdiv(da.nb, most);
         parts = cdiv(da.nb, da.bpp);
         da.dK = parts == 1 ? dK : nullptr;
         const int wlast = W - (da.bx - 1) * da.WB;
@@ -195,15 +246,16 @@ int launch_layer_backward(const float *x, const float *dy, const float *K, float
         da.d_nt = make_div(da.nt);
         da.d_w = make_div(da.WB);
         da.d_wl = make_div(wlast);
-        da.d_xw = make_div(da.WB + k - 1);
-        da.d_xwl = make_div(wlast + k - 1);
+        da.d_xw = make_div(da.WB + da.pc);
+        da.d_xwl = make_div(wlast + da.pc);
         da.parts = parts;
         da.d_nt2 = make_div(da.nt * da.nt);
         da.d_parts = make_div(parts);
+        da.d_yr = make_div(da.RB);
+        da.d_xr = make_div(da.RB + da.pr);
         da.blocks = da.nt * da.nt * parts * groups;
     }
     // one launch for both, but for images of 2 GB or more
-    const bool big = (long long)C * H * W * 4 >= (1ll << 31);
     const DkArgs none = {};
     const DkArgs &beside = big ? none : da;
     int rc = FINC_OK;
@@ -222,10 +274,11 @@ int launch_layer_backward(const float *x, const float *dy, const float *K, float
     if (rc == FINC_OK && da.blocks > 0 && (big || !dx)) {
         for_k(k, [&](auto kc) {
             constexpr int KC = decltype(kc)::value;
-            if (big)
-                hipLaunchKernelGGL((dk_kernel<KC, true>), dim3(da.blocks), dim3(256), 0, stream, da);
-            else
-                hipLaunchKernelGGL((dk_kernel<KC, false>), dim3(da.blocks), dim3(256), 0, stream, da);
+            auto *kernel = big                   ? dk_kernel<KC, kDkOne, true>
+                           : da.form == kDkCrop  ? dk_kernel<KC, kDkCrop, false>
+                           : da.form == kDkMulti ? dk_kernel<KC, kDkMulti, false>
+                                                 : dk_kernel<KC, kDkOne, false>;
+            hipLaunchKernelGGL(kernel, dim3(da.blocks), dim3(256), 0, stream, da);
         });
         rc = conv_launched();
     }

@@ -2306,11 +2306,11 @@ __global__ __launch_bounds__(MAXT) void forward_kernel(FwdArgs a) {
 // the other's gaps: 12 x 32 x 32, batch 64, with the parts' sum 20.1 us in two
 // launches, 15.3 in one (34.5 with dx as an implicit GEMM over K); 3 x 8 x 8 of
 // one image 8.9 and 5.2 (7.0).
-template <bool PADW, int KK>
+template <bool PADW, int KK, int FORM>
 __global__ __launch_bounds__(kFwdThreads) void grad_kernel(FwdArgs a, DkArgs dk) {
     extern __shared__ float sm[];
     if ((int)blockIdx.x < dk.blocks)
-        dk_tile<KK, false>(dk, blockIdx.x, sm);
+        dk_tile<KK, FORM, false>(dk, blockIdx.x, sm);
     else
         forward_block<PADW, false, true, false>(a, blockIdx.x - dk.blocks, sm);
 }
@@ -2988,10 +2988,17 @@ int finc_detail::layer_grads(const float *dy, float *dx, const float *K, int B, 
     const void *fk = nullptr;
     auto pick = [&](auto kc) {
         constexpr int KK = decltype(kc)::value;
-        fk = a.fp.padw ? reinterpret_cast<const void *>(grad_kernel<true, KK>)
-                       : reinterpret_cast<const void *>(grad_kernel<false, KK>);
-        if (dk.blocks > 0 && lds < dk_lds_floats<KK>() * sizeof(float))
-            lds = dk_lds_floats<KK>() * sizeof(float);
+        auto of = [&](auto padw) {
+            constexpr bool P = decltype(padw)::value;
+            return dk.form == kDkCrop    ? reinterpret_cast<const void *>(grad_kernel<P, KK, kDkCrop>)
+                   : dk.form == kDkMulti ? reinterpret_cast<const void *>(grad_kernel<P, KK, kDkMulti>)
+                                         : reinterpret_cast<const void *>(grad_kernel<P, KK, kDkOne>);
+        };
+        fk = a.fp.padw ? of(std::true_type{}) : of(std::false_type{});
+        const size_t need = (dk.form == kDkOne ? dk_lds_floats<KK, kDkOne>()
+                                               : dk_lds_floats<KK, kDkCrop>()) * sizeof(float);
+        if (dk.blocks > 0 && lds < need)
+            lds = need;
     };
     switch (k) {
     case 1: pick(std::integral_constant<int, 1>{}); break;

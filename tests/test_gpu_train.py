@@ -96,6 +96,37 @@ def test_layer_gradient_tiles(orc, shape, corner):
     assert torch.equal(finc.backward(dev(x), dev(dy), dev(K), corner, -1.0, want_dx=False)[1], dK)
 
 
+# Small images (several a band of dK; fewer rows or columns than the kernel; of
+# a pixel), with a band that holds fewer than the others; blocks of the input
+# gradient that take several images, of one (64 channels) and more a compute
+# unit; rows cut into segments of columns, the last one narrower.
+SMALL_SHAPES = [(1, 2, 2, 2, 3), (300, 3, 1, 1, 3), (70, 17, 2, 2, 3), (33, 5, 4, 4, 7),
+                (23, 16, 8, 8, 2), (45, 2, 3, 7, 4), (100, 4, 1, 5, 5), (50, 3, 7, 1, 6),
+                (1100, 3, 3, 3, 3), (300, 64, 3, 3, 3), (29, 33, 4, 3, 1), (2, 12, 3, 300, 3),
+                (1, 20, 2, 133, 2), (3, 1, 1, 515, 5)]
+
+
+@pytest.mark.parametrize("corner", [0, 1, 3])
+@pytest.mark.parametrize("shape", SMALL_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_layer_gradient_small_images(orc, shape, corner):
+    B, C, H, W, k = shape
+    rng = np.random.default_rng(C * 10 + corner)
+    x, dy = rng.normal(size=(B, C, H, W)), rng.normal(size=(B, C, H, W))
+    K = synth.garbage_in_mask(synth.masked_kernel(C, k, corner, 40 + C), corner, seed=k)
+    print("layer backward", shape, corner, flush=True)
+    dx, dK = finc.backward(dev(x), dev(dy), dev(K), corner, -1.0, dx=poisoned(x.shape),
+                           dK=poisoned(K.shape))
+    want_dx, want_dK = orc.backward(f64(x), f64(dy), f64(K), corner, -1.0)
+    assert_close(host(dx), want_dx, f"dx {shape}")
+    _, sq = orc.backward(f64(x) ** 2, f64(dy) ** 2, f64(K), corner, 0.0)
+    assert_close(host(dK), want_dK, f"dK {shape}", scale=np.sqrt(sq))
+    assert torch.equal(finc.backward(dev(x), dev(dy), dev(K), corner, want_dK=False)[0], dx)
+    assert torch.equal(finc.backward(dev(x), dev(dy), dev(K), corner, -1.0, want_dx=False)[1], dK)
+    # an image's dx does not depend on the batch
+    one = finc.backward(dev(x[-1:]), dev(dy[-1:]), dev(K), corner, want_dK=False)[0]
+    assert torch.equal(one[0], dx[-1])
+
+
 def test_unit_backward_workload(orc):
     """The unit workload's shape (256 images of 12 x 16 x 16, k = 3): dK4
     sums 65,536 pixels per tap; dx on three sampled images; dx alone and dK

@@ -99,3 +99,12 @@ def test_backward_grids(drive, want):
         assert rc == finc.OK and ls, (s, rc, ls)
         for n, blocks, threads, lds in ls:
             assert 0 < blocks * threads < 2**32 and lds <= LDS, (s, n, blocks, threads, lds)
+
+
+def test_backward_of_small_images(drive):
+    """Small images share dK's bands."""
+    shapes = [(4096, 12, 2, 2, 3), (96, 12, 4, 4, 3), (4096, 12, 1, 1, 3), (20000, 3, 4, 4, 3)]
+    (_, a), (_, b), (_, c), (_, d) = drive([("backward", 2, *s, 0) for s in shapes])
+    # dk_kernel<k, FORM, BIG>: 1 several images a band, 2 and less halo
+    for ls, form in ((a, 2), (b, 1), (c, 2), (d, 1)):
+        assert "9dk_kernelILi3ELi%dELb0E" % form in ls[0][0], ls
