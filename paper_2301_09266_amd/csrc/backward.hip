@@ -167,7 +167,7 @@ __global__ __launch_bounds__(256) void gemm_grad_kernel(ConvArgs ca, int gx, DkA
         return;
     }
     const int b = blockIdx.x - da.blocks;
-    conv_tile<R, WCO, NS>(ca, b % gx, b / gx, 0, lds);
+    conv_tile<R, WCO, NS, 4>(ca, b % gx, b / gx, 0, lds);
 }
 template <int R>
 void launch_gemm_grad(const ConvArgs &a, const DkArgs &da, hipStream_t st) {

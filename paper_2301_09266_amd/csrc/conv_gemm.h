@@ -75,18 +75,20 @@ constexpr int conv_kc() {
     return WCO == 4 ? 32 : 64;
 }
 
-// LDS floats of one block of the <WCO, NS, KC> configuration (rows of KC + 4
+// LDS floats of one block of the <WCO, NS> configuration (rows of conv_kc + 4
 // floats).
-template <int WCO, int NS, int KC = conv_kc<WCO>()>
+template <int WCO, int NS>
 constexpr int conv_lds_floats() {
-    return (16 * WCO + 16 * NS * (4 / WCO)) * (KC + 4);
+    return (16 * WCO + 16 * NS * (4 / WCO)) * (conv_kc<WCO>() + 4);
 }
 
 // One output tile (bx along pixels, by along c_out, bz the part of K) with
-// the block's LDS at lds (conv_lds_floats<WCO, NS, KC>() floats, 16-byte aligned).
-template <int R, int WCO, int NS, int KC = conv_kc<WCO>()>
+// the block's LDS at lds (conv_lds_floats<WCO, NS>() floats, 16-byte aligned).
+// ACC: accumulators of a sum, 1, or 4 (k mod 4, joined pairwise: a quarter of
+// the rounding chain, as the forward's sums).
+template <int R, int WCO, int NS, int ACC = 1>
 __device__ __forceinline__ void conv_tile(const ConvArgs &a, int bx, int by, int bz, float *lds) {
-    constexpr int BM = 16 * WCO, BN = 16 * NS * (4 / WCO);
+    constexpr int BM = 16 * WCO, BN = 16 * NS * (4 / WCO), KC = conv_kc<WCO>();
     constexpr int SK = KC + 4, KQ = KC / 4;   // row stride, quads per chunk row
     constexpr int TPP = kConvThreads / BN;   // threads per staged pixel
     constexpr int QPT = KQ / TPP;            // k quads per thread (B)
@@ -165,10 +167,12 @@ __device__ __forceinline__ void conv_tile(const ConvArgs &a, int bx, int by, int
                 make_float4(rb[u][0], rb[u][1], rb[u][2], rb[u][3]);
     };
 
-    f32x4 acc[NS];
+    f32x4 sum[ACC][NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s)
-        acc[s] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int v = 0; v < ACC; ++v)
+            sum[v][s] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     const int nall = (a.K + KC - 1) / KC;
     const int cbeg = a.partial ? bz * a.cps : 0;
     const int nchunk = a.partial ? min(a.cps, nall - cbeg) : nall;
@@ -186,10 +190,10 @@ __device__ __forceinline__ void conv_tile(const ConvArgs &a, int bx, int by, int
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 const float4 b4 = *reinterpret_cast<const float4 *>(brow + 16 * s * SK + 16 * blk);
-                acc[s] = mfma4(w4.x, b4.x, acc[s]);
-                acc[s] = mfma4(w4.y, b4.y, acc[s]);
-                acc[s] = mfma4(w4.z, b4.z, acc[s]);
-                acc[s] = mfma4(w4.w, b4.w, acc[s]);
+                sum[0][s] = mfma4(w4.x, b4.x, sum[0][s]);
+                sum[1 % ACC][s] = mfma4(w4.y, b4.y, sum[1 % ACC][s]);
+                sum[2 % ACC][s] = mfma4(w4.z, b4.z, sum[2 % ACC][s]);
+                sum[3 % ACC][s] = mfma4(w4.w, b4.w, sum[3 % ACC][s]);
             }
         }
         if (c + 1 < nchunk) {
@@ -198,6 +202,11 @@ __device__ __forceinline__ void conv_tile(const ConvArgs &a, int bx, int by, int
             __syncthreads();
         }
     }
+    f32x4 acc[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+        acc[s] = ACC == 4 ? (sum[0][s] + sum[1 % ACC][s]) + (sum[2 % ACC][s] + sum[3 % ACC][s])
+                          : sum[0][s];
     if (a.partial) {   // raw sums of this part of K
         float *pz = a.partial + (long long)bz * a.Co * Q;
 #pragma unroll
@@ -241,10 +250,10 @@ __device__ __forceinline__ void conv_tile(const ConvArgs &a, int bx, int by, int
     }
 }
 
-template <int R, int WCO, int NS, int KC = conv_kc<WCO>()>
+template <int R, int WCO, int NS>
 __global__ __launch_bounds__(kConvThreads) void conv_kernel(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) float lds[conv_lds_floats<WCO, NS, KC>()];
-    conv_tile<R, WCO, NS, KC>(a, blockIdx.x, blockIdx.y, blockIdx.z, lds);
+    __shared__ __attribute__((aligned(16))) float lds[conv_lds_floats<WCO, NS>()];
+    conv_tile<R, WCO, NS>(a, blockIdx.x, blockIdx.y, blockIdx.z, lds);
 }
 
 // The parts of a K-split convolution added in order (part 0 first), then

@@ -1913,23 +1913,31 @@ struct FwdArgs {
     // b' = 4 b + g is quarter g, with corner g and weights K + g C^2 k^2 (one
     // layer per block; four layers prepared)
     int split;
-    long long img;   // (FLIP) floats from one image to the next, in and out
+    // (FLIP) floats from one image to the next, in and out; (MANY) images; those
+    // that a block steps by; the image's columns, in nseg segments of the plan's W
+    long long img;
+    int B, step, Wt, nseg;
+    FastDiv d_per, d_nblk;   // blocks of an image, of a segment
     FwdPlan fp;
 };
 
 constexpr int kFwdThreads = 256;       // (preparation blocks and single layers)
 constexpr int kFwdUnitThreads = 512;
 constexpr int kFwdMinBlocks = 256;   // a block per compute unit of the chip
-constexpr long long kMaxGridThreads = (1ll << 32) - 1;
 
 // ROWS: how the weights reach LDS (units of several channel tiles; see below).
 // FLIP (one layer): K read transposed over channels and reversed in space,
 // K'[n][m][t] = K[m][n][k^2 - 1 - t], with K's masked entries zero: the layer's
-// input gradient is the forward of K' with the opposite corner.
+// input gradient is the forward of K' with the opposite corner.  FLIP 2 (MANY):
+// a block takes the same rows of several images where there are more than the
+// chip holds at a time (its weights are staged once), and rows may be cut into
+// segments of columns where there are too few (each with its halo); 0.2 to 0.3 us
+// a block more than FLIP 1.
 // PREP: the launch's first blocks may prepare weights (up to kFusedPrepMaxC
 // channels, one tile: never with ROWS).
-template <bool PADW, bool ROWS, bool FLIP, bool PREP>
+template <bool PADW, bool ROWS, int FLIP, bool PREP>
 __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block, float *sm) {
+    constexpr bool MANY = FLIP == 2;
     const FwdPlan &fp = a.fp;
     const int nprep = a.split ? 4 : fp.n;   // layers prepared
     const int npre = PREP && a.prepared ? nprep * a.ppl : 0;
@@ -1973,17 +1981,25 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nwaves = blockDim.x >> 6;
     const int bid = block - npre - (!FLIP && a.logdet ? 1 : 0);
-    const int b = bid / fp.nblk, blk = bid - b * fp.nblk;
+    int b, seg = 0, blk;
+    if constexpr (MANY) {
+        const int s = fdiv(bid, a.d_nblk);   // segment of all
+        blk = bid - s * fp.nblk;
+        b = fdiv(bid, a.d_per);
+        seg = s - b * a.nseg;
+    } else {
+        b = bid / fp.nblk;
+        blk = bid - b * fp.nblk;
+    }
+    const int Wt = MANY ? a.Wt : W, j0 = MANY ? seg * W : 0;
     const int corner0 = a.split ? (b & 3) : fp.corner0;   // this block's (first) corner
     const float *Kb = a.K + (a.split ? (size_t)(b & 3) * fp.C * fp.C * fp.K * fp.K : 0);
     const int i0 = blk * fp.RB, rb = imin(H, i0 + fp.RB) - i0, HB = fp.HB;
     float *X = sm + fp.offI;
     float4 *Wf = reinterpret_cast<float4 *>(sm + fp.offW);
     int *Dq = reinterpret_cast<int *>(sm + fp.offD);
-    const size_t HW = (size_t)H * W;
+    const size_t HW = (size_t)H * Wt;
     const size_t img = FLIP ? (size_t)a.img : C * HW;
-    const float *xb = a.in + (size_t)b * img;
-    float *yb = a.out + (size_t)b * img;
     // weight fragments: Wf[(nt NGw + g) 64 + lane].e = K[co][ci][tap] for
     // co = 16 nt + li, quad u = 4 g + kq (tap u / ncq, ci = 4 (u % ncq) + e),
     // the channel mask applied (self tap, number selft of K: ci <= co only),
@@ -2090,205 +2106,218 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
     } else {
         gload(0, threadIdx.x, gpre);
     }
-    // zero-bordered input rows i0 - HB .. i0 + rb + HB - 1: every element of
-    // the block is written once, with x where the taps of this launch read
-    // the image and zero elsewhere (outside the image, padding channels, and
-    // for a single layer the halo side its corner never reads).  Images
-    // past 2^31 bytes: one element an item, loads unconditional from clamped
-    // indices, eight in flight per thread.
-    {
-        int oh0, ow0;
-        self_tap(corner0, K, oh0, ow0);
-        const int up = fp.n == 1 ? oh0 : HB, down = fp.n == 1 ? P - oh0 : HB;
-        const int lo = imax(0, i0 - up), hi = imin(H, i0 + rb + down);   // rows read
-        const int nrow = rb + 2 * HB, plane = nrow * WP, total = CP * plane;
-        const FastDiv dpl = blk == fp.nblk - 1 ? fp.d_plane_last : fp.d_plane;
-        if ((long long)C * HW * 4 < (1LL << 31)) {
-            // (pixel, channel quad) items, pixel fastest: four raw buffer
-            // loads over the image's C H W floats each (32-bit offsets; reads
-            // past the image, padding channels included, return 0; a pixel
-            // outside the rows or columns read takes an offset past the
-            // end), then one 16-byte LDS store
-            const unsigned nrec = (unsigned)(C * HW * 4);
-            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<float *>(xb), (short)0, (int)nrec, kBufferWord3);
-            const int nitem = plane * (CP / 4);
-            constexpr int U = 2;
-            for (int base = threadIdx.x; base < nitem; base += U * blockDim.x) {
-                float v[U][4];
-                int dst[U];
+    // one image (MANY: the block's first one, or a later one, for which the
+    // weights are there)
+    auto image = [&](auto firstc) __attribute__((always_inline)) {
+        constexpr bool first = decltype(firstc)::value;
+        const float *xb = a.in + (size_t)b * img;
+        float *yb = a.out + (size_t)b * img;
+        // zero-bordered input rows i0 - HB .. i0 + rb + HB - 1: every element of
+        // the block is written once, with x where the taps of this launch read
+        // the image and zero elsewhere (outside the image, padding channels, and
+        // for a single layer the halo side its corner never reads).  Images
+        // past 2^31 bytes: one element an item, loads unconditional from clamped
+        // indices, eight in flight per thread.
+        {
+            int oh0, ow0;
+            self_tap(corner0, K, oh0, ow0);
+            const int up = fp.n == 1 ? oh0 : HB, down = fp.n == 1 ? P - oh0 : HB;
+            const int lo = imax(0, i0 - up), hi = imin(H, i0 + rb + down);   // rows read
+            const int nrow = rb + 2 * HB, plane = nrow * WP, total = CP * plane;
+            const FastDiv dpl = blk == fp.nblk - 1 ? fp.d_plane_last : fp.d_plane;
+            if ((long long)C * HW * 4 < (1LL << 31)) {
+                // (pixel, channel quad) items, pixel fastest: four raw buffer
+                // loads over the image's C H W floats each (32-bit offsets; reads
+                // past the image, padding channels included, return 0; a pixel
+                // outside the rows or columns read takes an offset past the
+                // end), then one 16-byte LDS store
+                const unsigned nrec = (unsigned)(C * HW * 4);
+                const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<float *>(xb), (short)0, (int)nrec, kBufferWord3);
+                const int nitem = plane * (CP / 4);
+                constexpr int U = 2;
+                for (int base = threadIdx.x; base < nitem; base += U * blockDim.x) {
+                    float v[U][4];
+                    int dst[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int idx = base + u * blockDim.x;
-                    const int q = fdiv(idx, dpl), px = idx - q * plane;
-                    const int pr = fdiv(px, fp.d_WP), pc = px - pr * WP;
-                    const int i = i0 - HB + pr, j = pc - P;
-                    const bool ok = idx < nitem && i >= lo && i < hi && j >= 0 && j < W;
-                    const unsigned off = ok ? (unsigned)(4 * q * HW + i * W + j) * 4u : nrec;
+                    for (int u = 0; u < U; ++u) {
+                        const int idx = base + u * blockDim.x;
+                        const int q = fdiv(idx, dpl), px = idx - q * plane;
+                        const int pr = fdiv(px, fp.d_WP), pc = px - pr * WP;
+                        const int i = i0 - HB + pr, j = j0 + pc - P;
+                        const bool ok = idx < nitem && i >= lo && i < hi && j >= 0 && j < Wt;
+                        const unsigned off = ok ? (unsigned)(4 * q * HW + i * Wt + j) * 4u : nrec;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        v[u][e] = __builtin_bit_cast(
-                            float, __builtin_amdgcn_raw_buffer_load_b32(
-                                       rs, (int)(ok ? off + (unsigned)(e * HW * 4) : nrec), 0, 0));
-                    dst[u] = idx < nitem ? px * CP + 4 * q : -1;
+                        for (int e = 0; e < 4; ++e)
+                            v[u][e] = __builtin_bit_cast(
+                                float, __builtin_amdgcn_raw_buffer_load_b32(
+                                           rs, (int)(ok ? off + (unsigned)(e * HW * 4) : nrec), 0, 0));
+                        dst[u] = idx < nitem ? px * CP + 4 * q : -1;
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            pin(v[u][e]);
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (dst[u] >= 0)
+                            *reinterpret_cast<float4 *>(X + dst[u]) =
+                                make_float4(v[u][0], v[u][1], v[u][2], v[u][3]);
                 }
+            } else {
+                constexpr int U = 8;
+                for (int base = threadIdx.x; base < total; base += U * blockDim.x) {
+                    float v[U];
+                    bool inb[U];
+                    int dst[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u)
+                    for (int u = 0; u < U; ++u) {
+                        const int idx = base + u * blockDim.x;
+                        const int c = fdiv(idx, dpl), rem = idx - c * plane;
+                        const int pr = fdiv(rem, fp.d_WP), pc = rem - pr * WP;
+                        const int i = i0 - HB + pr, j = j0 + pc - P;
+                        inb[u] = idx < total && c < C && i >= lo && i < hi && j >= 0 && j < Wt;
+                        v[u] = xb[inb[u] ? c * HW + (size_t)i * Wt + j : 0];
+                        dst[u] = idx < total ? rem * CP + c : -1;
+                    }
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        pin(v[u][e]);
+                    for (int u = 0; u < U; ++u)
+                        pin(v[u]);
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (dst[u] >= 0)
-                        *reinterpret_cast<float4 *>(X + dst[u]) =
-                            make_float4(v[u][0], v[u][1], v[u][2], v[u][3]);
-            }
-        } else {
-            constexpr int U = 8;
-            for (int base = threadIdx.x; base < total; base += U * blockDim.x) {
-                float v[U];
-                bool inb[U];
-                int dst[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int idx = base + u * blockDim.x;
-                    const int c = fdiv(idx, dpl), rem = idx - c * plane;
-                    const int pr = fdiv(rem, fp.d_WP), pc = rem - pr * WP;
-                    const int i = i0 - HB + pr, j = pc - P;
-                    inb[u] = idx < total && c < C && i >= lo && i < hi && j >= 0 && j < W;
-                    v[u] = xb[inb[u] ? c * HW + (size_t)i * W + j : 0];
-                    dst[u] = idx < total ? rem * CP + c : -1;
+                    for (int u = 0; u < U; ++u)
+                        if (dst[u] >= 0)
+                            X[dst[u]] = inb[u] ? v[u] : 0.0f;
                 }
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    pin(v[u]);
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (dst[u] >= 0)
-                        X[dst[u]] = inb[u] ? v[u] : 0.0f;
             }
         }
-    }
-    for (int q = 0; q < fp.n; ++q) {
-        const int corner = fp.n == 1 ? corner0 : q;
-        int oh, ow;
-        self_tap(corner, K, oh, ow);
-        // (K's self tap; with FLIP its corner is the opposite of this launch's)
-        const int selft = FLIP ? (P - oh) * K + P - ow : oh * K + ow;
-        if constexpr (ROWS) {
-            if (q == 0)
-                __syncthreads();   // the fragments' zeros
-            rstore(rpre, wave, selft);
-            for (int w = wave + kWU * nwaves; w < nwl; w += kWU * nwaves) {
-                u32x4 v[kWU];
-                rload(q, w, v);
-                rstore(v, w, selft);
-            }
-        } else {
-            int wb = threadIdx.x;
-            if (q == 0) {   // (the first round went out before the input)
-                gstore(gpre, wb, selft);
-                wb += 2 * blockDim.x;
-                if (!PADW && threadIdx.x < 64)   // the padding groups' zero fragment
-                    Wf[nfrag + threadIdx.x] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            }
-            for (; wb < nfrag; wb += 2 * blockDim.x) {
-                float v[2][4];
-                gload(q, wb, v);
+        for (int q = 0; q < fp.n; ++q) {
+            const int corner = fp.n == 1 ? corner0 : q;
+            int oh, ow;
+            self_tap(corner, K, oh, ow);
+            // (K's self tap; with FLIP its corner is the opposite of this launch's)
+            const int selft = FLIP ? (P - oh) * K + P - ow : oh * K + ow;
+            if constexpr (ROWS) {
+                if (q == 0)
+                    __syncthreads();   // the fragments' zeros
+                rstore(rpre, wave, selft);
+                for (int w = wave + kWU * nwaves; w < nwl; w += kWU * nwaves) {
+                    u32x4 v[kWU];
+                    rload(q, w, v);
+                    rstore(v, w, selft);
+                }
+            } else if constexpr (first) {
+                int wb = threadIdx.x;
+                if (q == 0) {   // (the first round went out before the input)
+                    gstore(gpre, wb, selft);
+                    wb += 2 * blockDim.x;
+                    if (!PADW && threadIdx.x < 64)   // the padding groups' zero fragment
+                        Wf[nfrag + threadIdx.x] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                }
+                for (; wb < nfrag; wb += 2 * blockDim.x) {
+                    float v[2][4];
+                    gload(q, wb, v);
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
+                    for (int h = 0; h < 2; ++h)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        pin(v[h][e]);
-                gstore(v, wb, selft);
+                        for (int e = 0; e < 4; ++e)
+                            pin(v[h][e]);
+                    gstore(v, wb, selft);
+                }
             }
-        }
-        // gather offset of quad u relative to the output pixel's address (taps
-        // reach up/left too: offsets are signed); padding quads, whose
-        // weights are zero, read the output pixel's own input (offset 0)
-        for (int u = threadIdx.x; u < fp.NG * 4; u += blockDim.x) {
-            const int t = fdiv(u, fp.d_ncq), cq = u - t * fp.ncq;
-            const int ka = fdiv(t, fp.d_K), kb = t - ka * K;
-            Dq[u] = u < fp.nq ? ((ka - oh) * WP + (kb - ow)) * CP + 4 * cq : 0;
-        }
-        __syncthreads();
-        const bool last = q == fp.n - 1;
-        if (ROWS && !last)
-            rload(q + 1, wave, rpre);
-        float *Yo = sm + fp.offO;
-        // rows of this layer's output the block computes, rlo .. rhi - 1: its
-        // own, and in a band of a unit also those its later layers read
-        // (TL: k-1 above for TR; TL, TR: 2(k-1) below for BL and BR; BL:
-        // k-1 below for BR), within the image
-        int rlo = i0, rhi = i0 + rb;
-        if (fp.n > 1 && fp.nblk > 1) {
-            rlo = imax(0, i0 - (q == 0 ? P : 0));
-            rhi = imin(H, i0 + rb + (q < 2 ? 2 * P : q == 2 ? P : 0));
-        }
-        const int npix = (rhi - rlo) * W, nitem = ceil_div(npix, 16) * fp.NT;
-        const int xrow = rlo - i0 + HB;   // staged row of output row rlo
-        for (int item = wave; item < nitem; item += nwaves) {
-            const int tile = fdiv(item, fp.d_NT), nt = item - tile * fp.NT;
-            const int p = tile * 16 + li;
-            const bool valid = p < npix;
-            const int pc = valid ? p : 0;
-            const int il = fdiv(pc, fp.d_W), j = pc - il * W;
-            const int base = ((il + xrow) * WP + j + P) * CP;
-            // four accumulators over the quad groups (group g -> g mod 4), joined
-            // pairwise: the rounding chain is a quarter as long as a single one
-            f32x4 part[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                part[v] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            // four groups at a time (NG is a multiple of four), without a
-            // branch: their offset reads, then their 16-byte gathers and
-            // weight reads, then their MFMAs
-            const float4 *S4 = reinterpret_cast<const float4 *>(sm);   // regions are 16-byte aligned
-            const int zf = fp.NT * fp.NGw;   // (!PADW) the zero fragment
-            for (int g0 = 0; g0 < fp.NG; g0 += 4) {
-                int d[4];
+            // gather offset of quad u relative to the output pixel's address (taps
+            // reach up/left too: offsets are signed); padding quads, whose
+            // weights are zero, read the output pixel's own input (offset 0)
+            for (int u = threadIdx.x; first && u < fp.NG * 4; u += blockDim.x) {
+                const int t = fdiv(u, fp.d_ncq), cq = u - t * fp.ncq;
+                const int ka = fdiv(t, fp.d_K), kb = t - ka * K;
+                Dq[u] = u < fp.nq ? ((ka - oh) * WP + (kb - ow)) * CP + 4 * cq : 0;
+            }
+            __syncthreads();
+            const bool last = q == fp.n - 1;
+            if (ROWS && !last)
+                rload(q + 1, wave, rpre);
+            float *Yo = sm + fp.offO;
+            // rows of this layer's output the block computes, rlo .. rhi - 1: its
+            // own, and in a band of a unit also those its later layers read
+            // (TL: k-1 above for TR; TL, TR: 2(k-1) below for BL and BR; BL:
+            // k-1 below for BR), within the image
+            int rlo = i0, rhi = i0 + rb;
+            if (fp.n > 1 && fp.nblk > 1) {
+                rlo = imax(0, i0 - (q == 0 ? P : 0));
+                rhi = imin(H, i0 + rb + (q < 2 ? 2 * P : q == 2 ? P : 0));
+            }
+            const int npix = (rhi - rlo) * W, nitem = ceil_div(npix, 16) * fp.NT;
+            const int xrow = rlo - i0 + HB;   // staged row of output row rlo
+            for (int item = wave; item < nitem; item += nwaves) {
+                const int tile = fdiv(item, fp.d_NT), nt = item - tile * fp.NT;
+                const int p = tile * 16 + li;
+                const bool valid = p < npix;
+                const int pc = valid ? p : 0;
+                const int il = fdiv(pc, fp.d_W), j = pc - il * W;
+                const int base = ((il + xrow) * WP + j + P) * CP;
+                // four accumulators over the quad groups (group g -> g mod 4), joined
+                // pairwise: the rounding chain is a quarter as long as a single one
+                f32x4 part[4];
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    d[v] = Dq[4 * (g0 + v) + kq];
-                float4 xv[4], wv[4];
+                    part[v] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                // four groups at a time (NG is a multiple of four), without a
+                // branch: their offset reads, then their 16-byte gathers and
+                // weight reads, then their MFMAs
+                const float4 *S4 = reinterpret_cast<const float4 *>(sm);   // regions are 16-byte aligned
+                const int zf = fp.NT * fp.NGw;   // (!PADW) the zero fragment
+                for (int g0 = 0; g0 < fp.NG; g0 += 4) {
+                    int d[4];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    xv[v] = S4[(fp.offI + base + d[v]) >> 2];
-                    const int f = PADW || g0 + v < fp.NGr ? nt * fp.NGw + g0 + v : zf;
-                    wv[v] = Wf[f * 64 + lane];
+                    for (int v = 0; v < 4; ++v)
+                        d[v] = Dq[4 * (g0 + v) + kq];
+                    float4 xv[4], wv[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        xv[v] = S4[(fp.offI + base + d[v]) >> 2];
+                        const int f = PADW || g0 + v < fp.NGr ? nt * fp.NGw + g0 + v : zf;
+                        wv[v] = Wf[f * 64 + lane];
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        part[v] = mfma4(wv[v].x, xv[v].x, part[v]);
+                        part[v] = mfma4(wv[v].y, xv[v].y, part[v]);
+                        part[v] = mfma4(wv[v].z, xv[v].z, part[v]);
+                        part[v] = mfma4(wv[v].w, xv[v].w, part[v]);
+                    }
                 }
+                const f32x4 acc = (part[0] + part[1]) + (part[2] + part[3]);
+                const int co0 = nt * 16 + 4 * kq;
+                if (last) {
+                    if (valid && (!MANY || j0 + j < Wt)) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    part[v] = mfma4(wv[v].x, xv[v].x, part[v]);
-                    part[v] = mfma4(wv[v].y, xv[v].y, part[v]);
-                    part[v] = mfma4(wv[v].z, xv[v].z, part[v]);
-                    part[v] = mfma4(wv[v].w, xv[v].w, part[v]);
+                        for (int r = 0; r < 4; ++r)
+                            if (co0 + r < C)
+                                yb[(co0 + r) * HW + (size_t)(rlo + il) * Wt + j0 + j] = acc[r];
+                    }
+                } else if (valid && co0 < CP) {
+                    *reinterpret_cast<f32x4 *>(Yo + (size_t)p * CP + co0) = acc;
                 }
             }
-            const f32x4 acc = (part[0] + part[1]) + (part[2] + part[3]);
-            const int co0 = nt * 16 + 4 * kq;
-            if (last) {
-                if (valid) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (co0 + r < C)
-                            yb[(co0 + r) * HW + (size_t)(rlo + il) * W + j] = acc[r];
+            if (!last) {   // this layer's output is the next one's input
+                __syncthreads();
+                for (int idx = threadIdx.x; idx < npix * CP / 4; idx += blockDim.x) {
+                    const int p = fdiv(idx, fp.d_cp4), c4 = idx - p * (CP / 4);
+                    const int il = fdiv(p, fp.d_W), j = p - il * W;
+                    reinterpret_cast<float4 *>(X)[((il + xrow) * WP + j + P) * (CP / 4) + c4] =
+                        reinterpret_cast<const float4 *>(Yo)[idx];
                 }
-            } else if (valid && co0 < CP) {
-                *reinterpret_cast<f32x4 *>(Yo + (size_t)p * CP + co0) = acc;
+                __syncthreads();
             }
         }
-        if (!last) {   // this layer's output is the next one's input
-            __syncthreads();
-            for (int idx = threadIdx.x; idx < npix * CP / 4; idx += blockDim.x) {
-                const int p = fdiv(idx, fp.d_cp4), c4 = idx - p * (CP / 4);
-                const int il = fdiv(p, fp.d_W), j = p - il * W;
-                reinterpret_cast<float4 *>(X)[((il + xrow) * WP + j + P) * (CP / 4) + c4] =
-                    reinterpret_cast<const float4 *>(Yo)[idx];
-            }
-            __syncthreads();
+    };
+    image(std::true_type{});
+    if constexpr (MANY)
+        while ((b += a.step) < a.B) {
+            __syncthreads();   // the rows of the image before have been read
+            image(std::false_type{});
         }
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -2298,7 +2327,7 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
 template <bool PADW, bool ROWS, int MAXT>
 __global__ __launch_bounds__(MAXT) void forward_kernel(FwdArgs a) {
     extern __shared__ float sm[];
-    forward_block<PADW, ROWS, false, MAXT == kFwdThreads && !ROWS>(a, blockIdx.x, sm);
+    forward_block<PADW, ROWS, 0, MAXT == kFwdThreads && !ROWS>(a, blockIdx.x, sm);
 }
 
 // The gradients of a layer: dK's blocks (none where it is not wanted), which take
@@ -2306,13 +2335,13 @@ __global__ __launch_bounds__(MAXT) void forward_kernel(FwdArgs a) {
 // the other's gaps: 12 x 32 x 32, batch 64, with the parts' sum 20.1 us in two
 // launches, 15.3 in one (34.5 with dx as an implicit GEMM over K); 3 x 8 x 8 of
 // one image 8.9 and 5.2 (7.0).
-template <bool PADW, int KK, int FORM>
+template <bool PADW, int KK, int FORM, bool MANY>
 __global__ __launch_bounds__(kFwdThreads) void grad_kernel(FwdArgs a, DkArgs dk) {
     extern __shared__ float sm[];
     if ((int)blockIdx.x < dk.blocks)
         dk_tile<KK, FORM, false>(dk, blockIdx.x, sm);
     else
-        forward_block<PADW, false, true, false>(a, blockIdx.x - dk.blocks, sm);
+        forward_block<PADW, false, MANY ? 2 : 1, false>(a, blockIdx.x - dk.blocks, sm);
 }
 
 bool valid_shape(int B, int C, int H, int W, int k) {
@@ -2977,22 +3006,62 @@ int finc_detail::layer_grads(const float *dy, float *dx, const float *K, int B, 
     a.out = dx;
     a.K = K;
     a.img = img;
-    if (!valid_shape(B, C, H, W, k))   // (the forward's bound on H W, which the caller has not)
+    // The implicit GEMM instead (both orders of sums are fixed, and the choice
+    // does not depend on B): one tap, two but for 17 to 32 channels, and images
+    // of a few pixels, which it packs into its tiles (us, here and GEMM: k = 1,
+    // 48 x 16 x 16, batch 64 7.2, 5.7; k = 2, 64 x 8 x 8 11.0, 8.8, 24 x 32 x 32
+    // 12.3, 16.4; k = 3, 12 x 2 x 2, batch 4096 16.8, 7.5); 2^24 pixels and more,
+    // past the forward's bound; rows that do not fit in LDS.
+    if (k == 1 || (k == 2 && ceil_div(C, 16) != 2) || (long long)H * W <= 8 ||
+        !valid_shape(B, C, H, W, k))
         return FINC_EUNSUPPORTED;
-    a.fp = make_fwd_plan(C, H, W, k, 1, 3 - corner, B, false);
-    // (a launch of 2^32 threads or more is refused: each image is a block here)
-    if ((long long)B * a.fp.nblk + dk.blocks > kMaxGridThreads / kFwdThreads)
+    const int opposite = 3 - corner;
+    a.fp = make_fwd_plan(C, H, W, k, 1, opposite, B, false);
+    if ((size_t)a.fp.lds_floats * sizeof(float) > kLdsBytes)
         return FINC_EUNSUPPORTED;
-    a.nfwd = B * a.fp.nblk;
+    // too few blocks: segments of 64 columns and more
+    a.nseg = 1;
+    a.Wt = W;
+    const long long n = (long long)B * a.fp.nblk;
+    if (n < kFwdMinBlocks && W >= 128) {
+        const int want = (int)((kFwdMinBlocks + n - 1) / n), Ws = ceil_div(W, imin(want, W / 64));
+        a.nseg = ceil_div(W, Ws);
+        a.fp = make_fwd_plan(C, H, Ws, k, 1, opposite, B * a.nseg, false);
+    }
+    // too many of few pixels, or with LDS for one a compute unit: as many as the
+    // chip holds, or larger ones if those are few enough.  (The others overlap
+    // better when they are dispatched one by one; a launch is less than 2^32
+    // threads.)
+    auto rounds = [&](const FwdPlan &p) {
+        const size_t lds = p.lds_floats * sizeof(float);
+        const int hold = p.RB * p.W < 64 || 2 * lds > kLdsBytes
+                             ? imin(4, (int)(kLdsBytes / lds)) * kFwdMinBlocks
+                             : 1 << 23;
+        return (int)(((long long)B * p.nblk * a.nseg + hold - 1) / hold);
+    };
+    if (rounds(a.fp) == 2 && a.nseg == 1) {
+        const FwdPlan p = make_fwd_plan(C, H, W, k, 1, opposite, 2 * B, false);
+        if (rounds(p) == 1)
+            a.fp = p;
+    }
+    a.B = B;
+    a.step = ceil_div(B, rounds(a.fp));
+    a.nfwd = a.step * a.fp.nblk * a.nseg;
+    const bool many = a.step < B || a.nseg > 1;
+    a.d_per = make_fastdiv(a.fp.nblk * a.nseg);
+    a.d_nblk = make_fastdiv(a.fp.nblk);
     size_t lds = (size_t)a.fp.lds_floats * sizeof(float);
     const void *fk = nullptr;
     auto pick = [&](auto kc) {
         constexpr int KK = decltype(kc)::value;
         auto of = [&](auto padw) {
             constexpr bool P = decltype(padw)::value;
-            return dk.form == kDkCrop    ? reinterpret_cast<const void *>(grad_kernel<P, KK, kDkCrop>)
-                   : dk.form == kDkMulti ? reinterpret_cast<const void *>(grad_kernel<P, KK, kDkMulti>)
-                                         : reinterpret_cast<const void *>(grad_kernel<P, KK, kDkOne>);
+            if (dk.form == kDkCrop)
+                return reinterpret_cast<const void *>(grad_kernel<P, KK, kDkCrop, true>);
+            if (dk.form == kDkMulti)
+                return reinterpret_cast<const void *>(grad_kernel<P, KK, kDkMulti, true>);
+            return many ? reinterpret_cast<const void *>(grad_kernel<P, KK, kDkOne, true>)
+                        : reinterpret_cast<const void *>(grad_kernel<P, KK, kDkOne, false>);
         };
         fk = a.fp.padw ? of(std::true_type{}) : of(std::false_type{});
         const size_t need = (dk.form == kDkOne ? dk_lds_floats<KK, kDkOne>()
@@ -3001,7 +3070,6 @@ int finc_detail::layer_grads(const float *dy, float *dx, const float *K, int B, 
             lds = need;
     };
     switch (k) {
-    case 1: pick(std::integral_constant<int, 1>{}); break;
     case 2: pick(std::integral_constant<int, 2>{}); break;
     case 3: pick(std::integral_constant<int, 3>{}); break;
     case 4: pick(std::integral_constant<int, 4>{}); break;

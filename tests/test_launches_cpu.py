@@ -94,7 +94,8 @@ def test_backward_grids(drive, want):
     (2^24 images of a pixel included), LDS of a workgroup, no empty grid."""
     shapes = [(1 << 24, 1, 2, 2, 3), ((1 << 24) - 1, 1, 1, 1, 3), (1 << 26, 4, 1, 1, 1),
               (1 << 20, 3, 2, 2, 3), (1, 1, 1, 1, 1), (64, 48, 8, 8, 3), (2, 64, 40, 40, 7),
-              (33, 23, 27, 19, 5), (1, 12, (1 << 24) + 5, 1, 2), (1, 1, (1 << 31) - 130, 1, 1)]
+              (33, 23, 27, 19, 5), (1, 12, (1 << 24) + 5, 1, 2), (1, 1, (1 << 31) - 130, 1, 1),
+              (1 << 24, 1, 3, 3, 3), ((1 << 24) + 7, 1, 8, 8, 3), (3, 5, 2, 1000, 4)]
     for s, (rc, ls) in zip(shapes, drive([("backward", want, *s, 3) for s in shapes])):
         assert rc == finc.OK and ls, (s, rc, ls)
         for n, blocks, threads, lds in ls:
@@ -102,9 +103,13 @@ def test_backward_grids(drive, want):
 
 
 def test_backward_of_small_images(drive):
-    """Small images share dK's bands."""
+    """Small images share dK's bands, a pixel's are a GEMM in dx, and no launch
+    has more blocks than the chip holds at a time however many images there are."""
     shapes = [(4096, 12, 2, 2, 3), (96, 12, 4, 4, 3), (4096, 12, 1, 1, 3), (20000, 3, 4, 4, 3)]
     (_, a), (_, b), (_, c), (_, d) = drive([("backward", 2, *s, 0) for s in shapes])
     # dk_kernel<k, FORM, BIG>: 1 several images a band, 2 and less halo
     for ls, form in ((a, 2), (b, 1), (c, 2), (d, 1)):
         assert "9dk_kernelILi3ELi%dELb0E" % form in ls[0][0], ls
+    (_, a), (_, b), (_, c), (_, d) = drive([("backward", 1, *s, 0) for s in shapes])
+    assert names(a) == names(c) == ["gemm"] and names(b) == names(d) == ["fwd"]
+    assert d[0][1] <= 1024
