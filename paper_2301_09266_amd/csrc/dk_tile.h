@@ -177,7 +177,7 @@ __device__ __forceinline__ void dk_tile(const DkArgs &a, int blk, float *lds) {
             off[t] = inside(tt, ta, tb) ? (ta * wx + tb) * 4 : 0;
         }
         __syncthreads();
-        for (int s = wave; s < steps; s += 4) {
+        auto step = [&](int s, auto end) __attribute__((always_inline)) {
             const int pos = 4 * s + kq, pp = min(pos, np - 1);
             int i = fdiv(pp, dw);
             const int j = pp - i * wb;
@@ -189,12 +189,24 @@ __device__ __forceinline__ void dk_tile(const DkArgs &a, int blk, float *lds) {
 #pragma unroll
             for (int t = 0; t < G; ++t)
                 bv[t] = xp[off[t]];
+            if constexpr (decltype(end)::value) {
+#pragma unroll
+                for (int t = 0; t < G; ++t)
+                    bv[t] = pos < np ? bv[t] : 0.0f;
+            }
 #pragma unroll
             for (int t = 0; t < G; ++t)
                 acc[t] = mfma4(av, bv[t], acc[t]);
             if constexpr (CROP)
                 acc[G] = mfma4(av, 0.0f, acc[G]);
-        }
+        };
+        // (a last step's positions past the band's end: dy = 0 times an infinite x
+        // would be NaN)
+        const int full = np >> 2;
+        for (int s = wave; s < full; s += 4)
+            step(s, std::false_type{});
+        if (full < steps && (full & 3) == wave)
+            step(full, std::true_type{});
     }
     // lane (kq, li) of a wave holds D_t[co 4 kq + rr][ci li]; the waves' sums in order
     __syncthreads();

@@ -2227,11 +2227,13 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
             }
             // gather offset of quad u relative to the output pixel's address (taps
             // reach up/left too: offsets are signed); padding quads, whose
-            // weights are zero, read the output pixel's own input (offset 0)
+            // weights are zero, read the output pixel's own input (offset 0), or
+            // for a gradient zeros, past every row (an infinite value times their
+            // weights would be NaN where the sum is infinite)
             for (int u = threadIdx.x; first && u < fp.NG * 4; u += blockDim.x) {
                 const int t = fdiv(u, fp.d_ncq), cq = u - t * fp.ncq;
                 const int ka = fdiv(t, fp.d_K), kb = t - ka * K;
-                Dq[u] = u < fp.nq ? ((ka - oh) * WP + (kb - ow)) * CP + 4 * cq : 0;
+                Dq[u] = u < fp.nq ? ((ka - oh) * WP + (kb - ow)) * CP + 4 * cq : FLIP ? 1 << 28 : 0;
             }
             __syncthreads();
             const bool last = q == fp.n - 1;
@@ -2267,6 +2269,8 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
                 // weight reads, then their MFMAs
                 const float4 *S4 = reinterpret_cast<const float4 *>(sm);   // regions are 16-byte aligned
                 const int zf = fp.NT * fp.NGw;   // (!PADW) the zero fragment
+                // (FLIP) zeros behind the rows: a padding quad's weights
+                const int zq = (fp.offW >> 2) + (PADW ? fp.NG * 64 - 16 : zf * 64);
                 for (int g0 = 0; g0 < fp.NG; g0 += 4) {
                     int d[4];
 #pragma unroll
@@ -2275,7 +2279,8 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
                     float4 xv[4], wv[4];
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        xv[v] = S4[(fp.offI + base + d[v]) >> 2];
+                        const int at = (fp.offI + base + d[v]) >> 2;
+                        xv[v] = S4[FLIP ? imin(at, zq) : at];
                         const int f = PADW || g0 + v < fp.NGr ? nt * fp.NGw + g0 + v : zf;
                         wv[v] = Wf[f * 64 + lane];
                     }

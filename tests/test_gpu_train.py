@@ -127,6 +127,31 @@ def test_layer_gradient_small_images(orc, shape, corner):
     assert torch.equal(one[0], dx[-1])
 
 
+@pytest.mark.parametrize("corner", [0, 3])
+@pytest.mark.parametrize("shape", [(2, 4, 5, 5, 3), (1, 4, 13, 17, 3), (3, 4, 1, 3, 3), (2, 4, 6, 7, 5)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_layer_gradient_infinities(orc, shape, corner):
+    """One infinite input value, at the last position of a band whose positions
+    are not a multiple of four: dK is infinite where a tap reads it and finite
+    elsewhere.  One infinite value of dy, in a channel that no masked weight
+    multiplies: the same for dx.  (Padding takes part in neither.)"""
+    B, C, H, W, k = shape
+    rng = np.random.default_rng(7)
+    x, dy = rng.normal(size=(B, C, H, W)), rng.normal(size=(B, C, H, W))
+    K = synth.masked_kernel(C, k, corner, 3)
+    xi, dyi = x.copy(), dy.copy()
+    xi[-1, 1, -1, -1], dyi[0, C - 1, H // 2, W // 2] = np.inf, -np.inf
+    print("infinities", shape, corner, flush=True)
+    dK = finc.backward(dev(xi), dev(dy), dev(K), corner, want_dx=False)[1]
+    dx = finc.backward(dev(x), dev(dyi), dev(K), corner, want_dK=False)[0]
+    for got, want, what in ((dK, orc.backward(f64(xi), f64(dy), f64(K), corner, 0.0)[1], "dK"),
+                            (dx, orc.backward(f64(x), f64(dyi), f64(K), corner, 0.0)[0], "dx")):
+        assert not np.isnan(want).any() and np.isinf(want).any()
+        inf = np.isinf(want)
+        assert np.array_equal(host(got)[inf], want[inf]), what
+        assert_close(np.where(inf, 0.0, host(got)), np.where(inf, 0.0, want), f"{what} {shape}")
+
+
 def test_unit_backward_workload(orc):
     """The unit workload's shape (256 images of 12 x 16 x 16, k = 3): dK4
     sums 65,536 pixels per tap; dx on three sampled images; dx alone and dK
