@@ -229,7 +229,7 @@ __device__ __forceinline__ void net_repair(const NetArgs &a, int layer, int f, f
 #pragma unroll
                 for (int t = 0; t < 3; ++t)
                     p[t] = __uint_as_float((unsigned)*reinterpret_cast<const uint16_t *>(h + t * PH) << 16);
-                x = p[0] < INFINITY ? (p[0] + p[1]) + p[2] : p[0];   // (h >= 0)
+                x = p[1] < INFINITY ? (p[0] + p[1]) + p[2] : p[1];   // (h >= 0: never NaN)
             }
         }
         s = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, x, s, 0, 0, 0);

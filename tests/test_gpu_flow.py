@@ -43,6 +43,21 @@ def test_conv1x1(orc, C):
     assert_round_trip(host(xr), f64(x), "1x1")
 
 
+def test_conv1x1_single_products():
+    """A diagonal matrix of 64 channels, on the bf16 matrix cores: each result is
+    one product, of which at most 2^-24 is dropped, rounded once more to fp32.
+    Random mantissas, and one whose low parts are all large and of one sign."""
+    rng = np.random.default_rng(8)
+    d = rng.uniform(1.0, 2.0, size=64) * 2.0 ** rng.integers(-20, 20, size=64)
+    x = rng.uniform(1.0, 2.0, size=(4, 64, 16, 16)) * rng.choice([-1.0, 1.0], size=(4, 64, 16, 16))
+    d[::4], x[:, ::4, ::2] = 1.0077972, 1.0077972
+    y = host(finc.conv1x1_forward(dev(x), dev(np.diag(d))))
+    want = f64(x) * f64(d)[None, :, None, None]
+    err = np.abs(y / want - 1.0).max()
+    print(f"single products: largest relative error {err:.3e}", flush=True)
+    assert err <= 2.0**-23
+
+
 STEP_CASES = [
     # (B, C, H, W, k, hid)
     (2, 4, 5, 7, 3, 8), (2, 12, 16, 16, 3, 32), (3, 24, 8, 8, 3, 64), (2, 48, 4, 4, 3, 96),
