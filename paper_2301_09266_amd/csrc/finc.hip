@@ -1913,12 +1913,15 @@ struct FwdArgs {
     // b' = 4 b + g is quarter g, with corner g and weights K + g C^2 k^2 (one
     // layer per block; four layers prepared)
     int split;
-    // (FLIP) floats from one image to the next, in and out; (MANY) images; those
-    // that a block steps by; the image's columns, in nseg segments of the plan's W
+    FwdPlan fp;
+};
+
+// (FLIP) floats from one image to the next, in and out; (MANY) images; those that
+// a block steps by; the image's columns, in nseg segments of the plan's W
+struct GradArgs : FwdArgs {
     long long img;
     int B, step, Wt, nseg;
     FastDiv d_per, d_nblk;   // blocks of an image, of a segment
-    FwdPlan fp;
 };
 
 constexpr int kFwdThreads = 256;       // (preparation blocks and single layers)
@@ -1936,7 +1939,8 @@ constexpr int kFwdMinBlocks = 256;   // a block per compute unit of the chip
 // PREP: the launch's first blocks may prepare weights (up to kFusedPrepMaxC
 // channels, one tile: never with ROWS).
 template <bool PADW, bool ROWS, int FLIP, bool PREP>
-__device__ __forceinline__ void forward_block(const FwdArgs &a, const int block, float *sm) {
+__device__ __forceinline__ void forward_block(
+    const std::conditional_t<FLIP != 0, GradArgs, FwdArgs> &a, const int block, float *sm) {
     constexpr bool MANY = FLIP == 2;
     const FwdPlan &fp = a.fp;
     const int nprep = a.split ? 4 : fp.n;   // layers prepared
@@ -1991,7 +1995,11 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
         b = bid / fp.nblk;
         blk = bid - b * fp.nblk;
     }
-    const int Wt = MANY ? a.Wt : W, j0 = MANY ? seg * W : 0;
+    int Wt = W, j0 = 0;
+    if constexpr (MANY) {
+        Wt = a.Wt;
+        j0 = seg * W;
+    }
     const int corner0 = a.split ? (b & 3) : fp.corner0;   // this block's (first) corner
     const float *Kb = a.K + (a.split ? (size_t)(b & 3) * fp.C * fp.C * fp.K * fp.K : 0);
     const int i0 = blk * fp.RB, rb = imin(H, i0 + fp.RB) - i0, HB = fp.HB;
@@ -1999,7 +2007,9 @@ __device__ __forceinline__ void forward_block(const FwdArgs &a, const int block,
     float4 *Wf = reinterpret_cast<float4 *>(sm + fp.offW);
     int *Dq = reinterpret_cast<int *>(sm + fp.offD);
     const size_t HW = (size_t)H * Wt;
-    const size_t img = FLIP ? (size_t)a.img : C * HW;
+    size_t img = C * HW;
+    if constexpr (FLIP != 0)
+        img = (size_t)a.img;
     // weight fragments: Wf[(nt NGw + g) 64 + lane].e = K[co][ci][tap] for
     // co = 16 nt + li, quad u = 4 g + kq (tap u / ncq, ci = 4 (u % ncq) + e),
     // the channel mask applied (self tap, number selft of K: ci <= co only),
@@ -2341,7 +2351,7 @@ __global__ __launch_bounds__(MAXT) void forward_kernel(FwdArgs a) {
 // launches, 15.3 in one (34.5 with dx as an implicit GEMM over K); 3 x 8 x 8 of
 // one image 8.9 and 5.2 (7.0).
 template <bool PADW, int KK, int FORM, bool MANY>
-__global__ __launch_bounds__(kFwdThreads) void grad_kernel(FwdArgs a, DkArgs dk) {
+__global__ __launch_bounds__(kFwdThreads) void grad_kernel(GradArgs a, DkArgs dk) {
     extern __shared__ float sm[];
     if ((int)blockIdx.x < dk.blocks)
         dk_tile<KK, FORM, false>(dk, blockIdx.x, sm);
@@ -2870,9 +2880,20 @@ int launch_forward(const float *x, float *y, const float *K, double *logdet, flo
     // 27.2 us, k = 5 63.8 -> 58.6 us).
     const bool wide = n > 1 && !fuse && B * a.fp.nblk <= kFwdMinBlocks;
     const int threads = wide ? kFwdUnitThreads : kFwdThreads;
+    // The weights in memory order: with these; with whole channel tiles; and with
+    // rows of K that are whole 32-byte sectors, at k = 2 or two tiles, but where
+    // four blocks a compute unit run at a time, which hide a fragment's latency
+    // (three with the rows in flight).  Time against fragments, over 256 blocks:
+    // 32, 48 and 64 channels, k = 3 0.90, 0.97 and 0.97, 24 0.97; 44 and 60, k = 2
+    // 0.84 and 0.83; else 17, 20, 33 and 40, k = 3 1.08, 1.10, 1.08 and 1.04, up to
+    // 1.3 for 800 images of 3 x 3.
+    const bool full = B * a.fp.nblk > 3 * kFwdMinBlocks && 4 * lds <= kLdsBytes;
+    const bool rows = n > 1 && a.fp.NT > 1 &&
+                      (wide || C % 16 == 0 ||
+                       (C * k * k % 8 == 0 && (k == 2 || a.fp.NT == 2) && !full));
     auto pick = [&](auto padw) -> const void * {
         constexpr bool P = decltype(padw)::value;
-        if (n > 1 && a.fp.NT > 1)
+        if (rows)
             return wide ? reinterpret_cast<const void *>(forward_kernel<P, true, kFwdUnitThreads>)
                         : reinterpret_cast<const void *>(forward_kernel<P, true, kFwdThreads>);
         return wide ? reinterpret_cast<const void *>(forward_kernel<P, false, kFwdUnitThreads>)
@@ -3005,7 +3026,7 @@ int scratch_of_device(void **out) {
 int finc_detail::layer_grads(const float *dy, float *dx, const float *K, int B, int C, int H,
                              int W, int k, int corner, long long img, const DkArgs &dk,
                              hipStream_t stream) {
-    FwdArgs a;
+    GradArgs a;
     memset(&a, 0, sizeof(a));
     a.in = dy;
     a.out = dx;

@@ -4,7 +4,7 @@
 // recorded instead of run.  No pointer given to the library is dereferenced on
 // the host.
 // Usage: launch_drive LIB, then lines "OP WANT B C H W k corner" on stdin, OP
-// backward (WANT: 1 dx, 2 dK, 3 both) or forward; per line one output line
+// backward (WANT: 1 dx, 2 dK, 3 both), forward or unit (the unit's forward); per line one output line
 // "rc;kernel,blocks,threads,lds;..." (the kernel's mangled name).
 // Test infrastructure: built and run by tests/test_launches_cpu.py.
 #include <dlfcn.h>
@@ -81,7 +81,8 @@ int main(int argc, char **argv) {
     }
     auto backward = reinterpret_cast<decltype(&finc_backward)>(dlsym(lib, "finc_backward"));
     auto forward = reinterpret_cast<decltype(&finc_forward)>(dlsym(lib, "finc_forward"));
-    if (!backward || !forward || names().empty())
+    auto unit = reinterpret_cast<decltype(&finc_unit_forward)>(dlsym(lib, "finc_unit_forward"));
+    if (!backward || !forward || !unit || names().empty())
         return 3;
     // buffers far apart, none of them there
     auto at = [](int i) { return reinterpret_cast<float *>((uintptr_t)(i + 1) << 40); };
@@ -89,9 +90,12 @@ int main(int argc, char **argv) {
     int want, B, C, H, W, k, corner;
     while (scanf("%31s %d %d %d %d %d %d %d", op, &want, &B, &C, &H, &W, &k, &corner) == 8) {
         launches.clear();
-        const int rc = std::string(op) == "forward"
+        const std::string o = op;
+        const int rc = o == "forward"
                            ? forward(at(0), at(1), at(2), nullptr, nullptr, B, C, H, W, k, corner,
                                      nullptr)
+                       : o == "unit"
+                           ? unit(at(0), at(1), at(2), nullptr, nullptr, B, C, H, W, k, nullptr)
                            : backward(at(0), at(1), at(2), want & 1 ? at(3) : nullptr,
                                       want & 2 ? at(4) : nullptr, -1.0, B, C, H, W, k, corner, at(5),
                                       nullptr);

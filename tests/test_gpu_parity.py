@@ -363,6 +363,21 @@ def test_unit_forward_weight_rows(orc, shape):
     assert torch.equal(inplace, y)
 
 
+@pytest.mark.parametrize("shape", [(260, 32, 3, 4, 3), (300, 24, 4, 4, 3), (800, 24, 3, 3, 2),
+                                   (300, 40, 3, 3, 3)], ids=lambda s: "x".join(map(str, s)))
+def test_unit_forward_weight_forms(orc, shape):
+    """More than 256 blocks: weights in memory order and by fragments; an image's
+    bits are those it has alone (512 threads, memory order)."""
+    B, C, H, W, k = shape
+    c = synth.unit_case(B, C, H, W, k)
+    K4 = np.stack([synth.garbage_in_mask(c["K4"][q], q, seed=q) for q in range(4)])
+    print("unit forward", shape, flush=True)
+    y = finc.unit_forward(dev(c["x"]), dev(K4), out=poisoned(c["x"].shape))
+    pick = [0, B - 1]
+    assert_close(host(y)[pick], orc.unit_forward(f64(c["x"][pick]), f64(K4)), f"unit {shape}")
+    assert torch.equal(finc.unit_forward(dev(c["x"][-1:]), dev(K4))[0], y[-1])
+
+
 @pytest.mark.parametrize("shape", [(2, 3, 5, 7, 3), (3, 12, 16, 16, 3), (1, 7, 9, 6, 5),
                                    (2, 4, 6, 6, 1), (2, 5, 8, 11, 2), (1, 20, 9, 10, 7),
                                    (2, 64, 5, 6, 3), (1, 33, 7, 5, 4), (3, 2, 11, 4, 6)],

@@ -113,3 +113,16 @@ def test_backward_of_small_images(drive):
     (_, a), (_, b), (_, c), (_, d) = drive([("backward", 1, *s, 0) for s in shapes])
     assert names(a) == names(c) == ["gemm"] and names(b) == names(d) == ["fwd"]
     assert d[0][1] <= 1024
+
+
+def test_unit_forward_instances(drive):
+    """forward_kernel<PADW, ROWS, threads>: 512 threads and weights in memory order
+    up to 256 blocks; beyond, memory order only for whole channel tiles or whole
+    sectors a row, and not where four blocks a compute unit run."""
+    shapes = [((64, 20, 8, 8, 3), "ELb1ELi512E"), ((800, 20, 4, 4, 3), "ELb0ELi256E"),
+              ((300, 33, 6, 6, 3), "ELb0ELi256E"), ((300, 40, 6, 6, 3), "ELb0ELi256E"),
+              ((300, 32, 4, 4, 3), "ELb1ELi256E"), ((300, 24, 8, 8, 3), "ELb1ELi256E"),
+              ((1000, 24, 3, 3, 2), "ELb0ELi256E"), ((300, 44, 4, 4, 2), "ELb1ELi256E"),
+              ((256, 12, 16, 16, 3), "ELb0ELi512E")]
+    for (s, want), (rc, ls) in zip(shapes, drive([("unit", 0, *s, 0) for s, _ in shapes])):
+        assert rc == finc.OK and "14forward_kernelILb1" + want in ls[0][0], (s, ls)
