@@ -106,7 +106,7 @@ __global__ __launch_bounds__(256) void net_pack_kernel(PackArgs a) {
     unsigned p[4][3];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-        split2(v[2 * j], v[2 * j + 1], p[j]);
+        split2<false>(v[2 * j], v[2 * j + 1], p[j]);
     u32x4 *o = reinterpret_cast<u32x4 *>(a.out + blockIdx.y * a.os) + (i >> 6) * 192 + l;
 #pragma unroll
     for (int t = 0; t < 3; ++t)
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(kNetThreads, 2) void coupling_net_kernel(NetArgs a)
             unsigned w[4][3];
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                split2(x[2 * i], x[2 * i + 1], w[i]);
+                split2<false>(x[2 * i], x[2 * i + 1], w[i]);
 #pragma unroll
             for (int t = 0; t < 3; ++t)
                 *reinterpret_cast<u32x4 *>(Xs + t * PX + o * kNetOct + l32 * 16) =
@@ -295,8 +295,8 @@ __global__ __launch_bounds__(kNetThreads, 2) void coupling_net_kernel(NetArgs a)
                 v[e] = fmaxf(acc[4 * g + e] + b[e], 0.0f);
             }
             unsigned p[2][3];
-            split2(v[0], v[1], p[0]);
-            split2(v[2], v[3], p[1]);
+            split2<true>(v[0], v[1], p[0]);
+            split2<true>(v[2], v[3], p[1]);
 #pragma unroll
             for (int t = 0; t < 3; ++t)
                 *reinterpret_cast<uint2 *>(Hs + t * PH + (4 * f + g) * kNetOct + l32 * 16 + lh * 8) =

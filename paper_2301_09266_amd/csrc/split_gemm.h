@@ -50,13 +50,18 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 // Two floats into their three bf16 parts (the first in the low half), each part
-// what is left rounded to nearest; the first one never rounds to infinity.
+// what is left rounded to nearest.  KEPT: the first one does not round to
+// infinity, so that the parts' sum is the value again (coupling_net.h holds h1 and
+// h2 as parts alone, and the same products are taken here); else a sum with such
+// a value is not finite and computed again from memory.
+template <bool KEPT>
 __device__ __forceinline__ void split2(float x, float y, unsigned (&w)[3]) {
     constexpr float kMax = 0x1.fefffep127f;   // the largest that rounds to a finite bf16
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
-        const f32x2 v = {t == 0 ? __builtin_amdgcn_fmed3f(x, -kMax, kMax) : x,
-                         t == 0 ? __builtin_amdgcn_fmed3f(y, -kMax, kMax) : y};
+        const bool cap = KEPT && t == 0;
+        const f32x2 v = {cap ? __builtin_amdgcn_fmed3f(x, -kMax, kMax) : x,
+                         cap ? __builtin_amdgcn_fmed3f(y, -kMax, kMax) : y};
         w[t] = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
         if (t < 2) {
             x -= __uint_as_float(w[t] << 16);
@@ -174,11 +179,11 @@ __global__ __launch_bounds__(256, 2) void split_gemm_kernel(ConvArgs a, int nco)
             }
         }
     };
-    auto put = [&](const float (&v)[8], char *dst, int plane) __attribute__((always_inline)) {
+    auto put = [&](const float (&v)[8], char *dst, int plane, auto kept) __attribute__((always_inline)) {
         unsigned w[4][3];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            split2(v[2 * i], v[2 * i + 1], w[i]);
+            split2<decltype(kept)::value>(v[2 * i], v[2 * i + 1], w[i]);
 #pragma unroll
         for (int t = 0; t < 3; ++t)
             *reinterpret_cast<u32x4 *>(dst + t * plane) = u32x4{w[0][t], w[1][t], w[2][t], w[3][t]};
@@ -189,10 +194,11 @@ __global__ __launch_bounds__(256, 2) void split_gemm_kernel(ConvArgs a, int nco)
 #pragma unroll
         for (int u = 0; u < UA; ++u)
             put(va[u], TROWS ? As + (ao + u * (256 / BM)) * OA + arow * 16
-                             : As + ao * OA + (arow + u * (256 / NO)) * 16, PA);
+                             : As + ao * OA + (arow + u * (256 / NO)) * 16, PA,
+                std::false_type{});
 #pragma unroll
         for (int u = 0; u < UB; ++u)
-            put(vb[u], Bs + (bo + (256 / BN) * u) * OB + bpx * 16, PB);
+            put(vb[u], Bs + (bo + (256 / BN) * u) * OB + bpx * 16, PB, std::integral_constant<bool, R == 1>{});
     };
 
     f32x16 hi[FM][FN], lo[FM][FN];
