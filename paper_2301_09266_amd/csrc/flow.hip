@@ -478,11 +478,18 @@ NetShape net_shape(const StepLayout &L) {
     return n;
 }
 
-// How many Steps' networks, at most n, the scratch holds packed; 0: hid is
+// Whether the network's convolutions are split: hid fits the one launch's LDS, and
+// is not so small that nearly all of its 32-channel fragments are padding (forward
+// Step of 12 x 16 x 16, batch 128, split and by the fp32 instruction: hid = 4 58.7,
+// 41.6 us, 8 58.6, 44.9, 32 59.0, 59.6; 24 x 8 x 8, batch 100: 4 33.9, 38.7, 8 33.9,
+// 42.5).
+bool net_split(const StepLayout &L) { return L.hid >= 8 && L.hid <= kNetMaxHid; }
+
+// How many Steps' networks, at most n, the scratch holds packed; 0: not split, hid is
 // too wide for the kernel's LDS, or not one fits (few pixels, B H W below
 // about 1,000 at hid = 512): the convolutions then run one by one.
 int net_room(const StepLayout &L, int B, int H, int W, int n) {
-    const long long room = L.hid <= kNetMaxHid ? 2ll * B * L.hid * H * W / net_shape(L).floats : 0;
+    const long long room = net_split(L) ? 2ll * B * L.hid * H * W / net_shape(L).floats : 0;
     return (int)(room < n ? room : n);
 }
 
@@ -551,9 +558,9 @@ int coupling_net(const float *v, long long vs, const float *sp, const StepLayout
                                                 sp + L.ls3, B, L.C, H, W, st)
                              : rc;
     }
-    // one by one; up to kNetMaxHid by the kernels that give the one launch's
-    // bits, so that results do not depend on which of the two a batch takes
-    const bool same = L.hid <= kNetMaxHid;
+    // one by one; where the one launch is for other batches by the kernels that
+    // give its bits, so that results do not depend on which of the two is taken
+    const bool same = net_split(L);
     int rc = launch_conv(v, vs, s.t1, (long long)L.hid * hw, sp + L.w1, sp + L.b1, nullptr, 1, B,
                          L.Ch, L.hid, H, W, 3, st, nullptr, same);
     if (rc == FINC_OK)
@@ -561,7 +568,7 @@ int coupling_net(const float *v, long long vs, const float *sp, const StepLayout
                          sp + L.b2, nullptr, 1, B, L.hid, L.hid, H, W, 1, st, nullptr, same);
     if (rc != FINC_OK)
         return rc;
-    if (same || 9 * L.C >= 64)
+    if (same || (9 * L.C >= 64 && L.hid >= 64))
         return launch_conv_taps(s.t2, (long long)L.hid * hw, s.hh, (long long)L.C * hw,
                                 sp + L.w3, sp + L.b3, sp + L.ls3, B, L.hid, L.C, H, W, st,
                                 s.part);

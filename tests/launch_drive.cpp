@@ -4,7 +4,8 @@
 // recorded instead of run.  No pointer given to the library is dereferenced on
 // the host.
 // Usage: launch_drive LIB, then lines "OP WANT B C H W k corner" on stdin, OP
-// backward (WANT: 1 dx, 2 dK, 3 both), forward or unit (the unit's forward); per line one output line
+// backward (WANT: 1 dx, 2 dK, 3 both), forward, unit (the unit's forward) or step
+// (the Step's forward, WANT the network's width); per line one output line
 // "rc;kernel,blocks,threads,lds;..." (the kernel's mangled name).
 // Test infrastructure: built and run by tests/test_launches_cpu.py.
 #include <dlfcn.h>
@@ -82,7 +83,8 @@ int main(int argc, char **argv) {
     auto backward = reinterpret_cast<decltype(&finc_backward)>(dlsym(lib, "finc_backward"));
     auto forward = reinterpret_cast<decltype(&finc_forward)>(dlsym(lib, "finc_forward"));
     auto unit = reinterpret_cast<decltype(&finc_unit_forward)>(dlsym(lib, "finc_unit_forward"));
-    if (!backward || !forward || !unit || names().empty())
+    auto step = reinterpret_cast<decltype(&finc_step_forward)>(dlsym(lib, "finc_step_forward"));
+    if (!backward || !forward || !unit || !step || names().empty())
         return 3;
     // buffers far apart, none of them there
     auto at = [](int i) { return reinterpret_cast<float *>((uintptr_t)(i + 1) << 40); };
@@ -94,6 +96,9 @@ int main(int argc, char **argv) {
         const int rc = o == "forward"
                            ? forward(at(0), at(1), at(2), nullptr, nullptr, B, C, H, W, k, corner,
                                      nullptr)
+                       : o == "step"
+                           ? step(at(0), at(1), nullptr, at(2), at(3), B, C, H, W, k, want, at(5),
+                                  nullptr)
                        : o == "unit"
                            ? unit(at(0), at(1), at(2), nullptr, nullptr, B, C, H, W, k, nullptr)
                            : backward(at(0), at(1), at(2), want & 1 ? at(3) : nullptr,

@@ -126,3 +126,18 @@ def test_unit_forward_instances(drive):
               ((256, 12, 16, 16, 3), "ELb0ELi512E")]
     for (s, want), (rc, ls) in zip(shapes, drive([("unit", 0, *s, 0) for s, _ in shapes])):
         assert rc == finc.OK and "14forward_kernelILb1" + want in ls[0][0], (s, ls)
+
+
+def test_step_network_launches(drive):
+    """The network in one launch where its scratch holds the packed weights, else
+    the split GEMMs; not split below 8 channels (fp32 instruction) and, layer by
+    layer, above 512."""
+    def run(B, C, H, hid):
+        rc, ls = drive([("step", hid, B, C, H, H, 3, 0)])[0]
+        assert rc == finc.OK and all(b * t < 2**32 and s <= LDS for _, b, t, s in ls)
+        return " ".join(n for n, _, _, _ in ls)
+    for case, one, split in (((100, 12, 16, 512), True, False), ((1, 12, 8, 512), False, True),
+                             ((128, 12, 16, 8), True, False), ((128, 12, 16, 7), False, False),
+                             ((64, 64, 4, 64), True, True), ((100, 12, 16, 513), False, True)):
+        k = run(*case)
+        assert ("coupling_net_kernel" in k) == one and ("split_gemm_kernel" in k) == split, (case, k)
