@@ -9,13 +9,16 @@
 //   dx[ci, s, t] = sum_{co, a, b} K[co][ci][a][b] dy[co, s - a + oh, t - b + ow]
 //     -- a convolution of dy with the kernel transposed over channels and
 //     flipped in space: the forward of that kernel with the opposite corner
-//     (layer_dx of finc_detail.h);
+//     (layer_grads of finc_detail.h), or an implicit GEMM where that is faster
+//     or does not fit (gemm_grad_kernel);
 //   dK[co][ci][a][b] = sum over images and pixels of dy[co, i, j] times the
 //     input the tap read (zero outside the image) -- a GEMM with
 //     M = C_out, N = C_in k^2 and a reduction over the B H W positions, in
-//     parts of the positions (dk_kernel), which dk_reduce_kernel adds in
+//     parts of the positions (dk_tile.h), which dk_reduce_kernel adds in
 //     order, sets the masked entries to 0 and adds the log|det| term
 //     gld H W / K[c][c][self] on the self diagonal.
+// Both run in one launch, or dK in one of its own (dk_kernel) where dx is not
+// wanted.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -153,10 +156,9 @@ bool valid_bwd_shape(int B, int C, int H, int W, int k) {
     return (long long)B * C * H * W < (1ll << 31);
 }
 
-// Both gradients where the forward's row blocks do not fit in LDS (very wide
-// rows, or many channels with a wide kernel): dx as the implicit GEMM of
-// conv_gemm.h on K read transposed and flipped, beside dK's blocks (da.blocks of
-// them, or none).  dx in tiles of 64 c_out x 64 pixels at 64 channels, else
+// Both gradients where layer_grads refuses (one or two taps, images of a few
+// pixels, rows that do not fit in LDS): dx as the implicit GEMM of conv_gemm.h on
+// K read transposed and flipped, beside dK's blocks (da.blocks of them, or none).  dx in tiles of 64 c_out x 64 pixels at 64 channels, else
 // 16 x 128, or 16 x 64 while there are fewer than two blocks a compute unit.
 template <int R, int WCO, int NS, int FORM>
 __global__ __launch_bounds__(256) void gemm_grad_kernel(ConvArgs ca, int gx, DkArgs da) {

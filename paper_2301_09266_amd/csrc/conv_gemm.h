@@ -1,7 +1,9 @@
 // conv_gemm.h -- an R x R convolution with per-axis offsets as an fp32 MFMA
-// implicit GEMM on gfx950 (v_mfma_f32_16x16x4_f32), shared by the full flow
-// (coupling and prior networks, the 1x1 convolution) and the backward of the
-// masked layer (its input gradient, a convolution of the output gradient).
+// implicit GEMM on gfx950 (v_mfma_f32_16x16x4_f32), shared by the full flow (the
+// narrow convolutions: fewer than 64 output channels) and the backward of the
+// masked layer (its input gradient, a convolution of the output gradient, where
+// it does not run as the forward), and the shifted sum of the taps' products
+// that the wide ones (split_gemm.h, coupling_net.h) end with.
 //
 //   y[b][co][i][j] = act(bias[co] + sum_{ci,a,c} Wt[co][ci][a][c] *
 //                        x[b][ci][i + a - ph][j + c - pw]) * oscale[co]
@@ -12,14 +14,14 @@
 // batch (q = b H W + p), so a block's tile may span images.
 //
 // Block: 256 threads, 4 waves arranged WCO (along c_out) x 4 / WCO (along
-// pixels); each wave computes 16 c_out x 16 NS pixels (NS accumulators).
-// K is staged 64 values at a time: A[co][k] (weights) and B[px][k] (the
-// gathered input window, im2col on the fly), rows padded to 68 floats, the
-// next chunk's global loads in flight during the current chunk's MFMAs.
-// Within one 16-wide slice of k, lane group kq takes k = 4 kq .. 4 kq + 3 as
-// the four MFMAs' k (one float4 LDS read each for A and B).  A long K may be
-// split into parts (blockIdx.z) whose raw sums a second kernel adds in order.
-// Every summation order is fixed: results are bitwise deterministic.
+// pixels); each wave computes 16 c_out x 16 NS pixels.  K is staged conv_kc
+// values at a time (32 or 64): A[co][k] (weights) and B[px][k] (the gathered
+// input window, im2col on the fly), rows padded by four floats, the next chunk's
+// global loads in flight during the current chunk's MFMAs.  Within one 16-wide
+// slice of k, lane group kq takes k = 4 kq .. 4 kq + 3 as the four MFMAs' k (one
+// float4 LDS read each for A and B).  A long K may be split into parts
+// (blockIdx.z) whose raw sums a second kernel adds in order.  Every summation
+// order is fixed: results are bitwise deterministic.
 #ifndef FINC_CONV_GEMM_H
 #define FINC_CONV_GEMM_H
 
@@ -65,7 +67,6 @@ struct ConvArgs {
 };
 
 constexpr int kConvThreads = 256;
-constexpr int kSK = 68;     // LDS row stride (floats) of 64-value k chunks
 
 // k values staged at a time (KC): 32 for the 64 c_out x 64 px tile (half the
 // LDS of 64, so twice the blocks a compute unit holds), 64 for the narrow

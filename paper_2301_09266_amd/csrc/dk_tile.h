@@ -13,18 +13,18 @@ namespace finc_detail {
 // dy[co][pos] x[ci][pos + tap t].  A block takes one tile of 16 c_out x 16 c_in
 // with up to nine taps over a part of the positions, in bands of up to 256
 // positions of an image, or of several whole small images, one below the other
-// (a band costs its latencies however few positions it has).  dy and x, with the k - 1 halo rows and columns its
-// corner reads, are staged in LDS as [channel quad][pixel][4], so a tap is an
-// LDS offset.  A step is four positions: one A read, then a B read and a
+// (a band costs its latencies however few positions it has).  dy and x, with the
+// k - 1 halo rows and columns its corner reads, are staged in LDS as
+// [channel quad][pixel][4], so a tap is an LDS offset.  A step is four positions: one A read, then a B read and a
 // v_mfma_f32_16x16x4_f32 a tap; the four waves take the steps in turn and their
 // sums meet in order.  Part z covers bands [z bpp, (z+1) bpp) and writes its sums
 // to partial + z C (C k^2); a single part writes dK itself.
 //
 // What bounds it: a few memory latencies and two barriers a band, and the matrix
 // instructions (32 cycles a tap and four positions).  With the sum of the parts,
-// 12 x 32 x 32, batch 64: 12.9 us, 48 x 8 x 8, batch 256: 31.4 us; staged column
-// by column, with k^2 gathers and their index arithmetic an input value, 23.5 and
-// 49.3 us; a band's reads a step ahead with running indices instead of the
+// 12 x 32 x 32, batch 64: 13.3 us, 48 x 8 x 8, batch 256: 26.9 us; staged column
+// by column, with k^2 gathers and their index arithmetic an input value, 23.6 and
+// 49.6 us; a band's reads a step ahead with running indices instead of the
 // divisions 14.8 us (more registers, no less time).
 struct DkArgs {
     const float *x, *dy, *K;

@@ -2065,7 +2065,7 @@ __device__ __forceinline__ void forward_block(
     // goes to its fragment -- 256 bytes a quad, so its address is linear in the
     // quad -- with a 4-byte LDS store.  Fragment by fragment a load of a wave
     // meets 64 lines, eight of them in flight.  Units, with the wider workgroups
-    // of launch_forward: 24 x 16 x 16 38.5 -> 30.0 us, 48 x 8 x 8 69 -> 50 us
+    // of launch_forward: 24 x 16 x 16 40.2 -> 31.0 us, 48 x 8 x 8 69 -> 49 us
     // (batch 64); a single layer, or one tile, has too few weights to gain
     // (23 x 27 x 19 12.4 -> 15.0 us).
     constexpr int kWU = 4;   // a wave's loads in flight
@@ -2347,9 +2347,9 @@ __global__ __launch_bounds__(MAXT) void forward_kernel(FwdArgs a) {
 
 // The gradients of a layer: dK's blocks (none where it is not wanted), which take
 // longer, then dx's.  One launch, so that the latency-bound blocks of either fill
-// the other's gaps: 12 x 32 x 32, batch 64, with the parts' sum 20.1 us in two
-// launches, 15.3 in one (34.5 with dx as an implicit GEMM over K); 3 x 8 x 8 of
-// one image 8.9 and 5.2 (7.0).
+// the other's gaps: 12 x 32 x 32, batch 64, with the parts' sum 8.0 and 13.3 us
+// alone, 16.1 in one (35.2 with dx as an implicit GEMM over K); 3 x 8 x 8 of one
+// image 4.2 and 5.4, 5.9 (7.4).
 template <bool PADW, int KK, int FORM, bool MANY>
 __global__ __launch_bounds__(kFwdThreads) void grad_kernel(GradArgs a, DkArgs dk) {
     extern __shared__ float sm[];
@@ -2876,8 +2876,8 @@ int launch_forward(const float *x, float *y, const float *K, double *logdet, flo
         return rc;
     // A unit whose grid leaves a compute unit at most one block (and whose
     // preparation blocks are not of kFwdThreads) takes twice the waves: a block's
-    // four phases then have two a SIMD (12 x 32 x 32, batch 64: k = 3 29.1 ->
-    // 27.2 us, k = 5 63.8 -> 58.6 us).
+    // four phases then have two a SIMD (12 x 32 x 32, batch 64: k = 3 29.9 ->
+    // 24.7 us, k = 5 64.6 -> 54.2 us).
     const bool wide = n > 1 && !fuse && B * a.fp.nblk <= kFwdMinBlocks;
     const int threads = wide ? kFwdUnitThreads : kFwdThreads;
     // The weights in memory order: with these; with whole channel tiles; and with

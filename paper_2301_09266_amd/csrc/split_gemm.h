@@ -25,8 +25,8 @@
 //
 // What bounds it: six 32x32x16 bf16 instructions (32 cycles each) do the work
 // of eight 32x32x2 fp32 ones (64 cycles each), 2.7 times the fp32 rate; the
-// splits' vector work and one barrier a chunk leave half of that.  512 -> 512
-// 1x1 on 25,600 pixels: 192 -> 95 us (141 TFLOP/s).
+// splits' vector work and one barrier a chunk leave half of that.  520 -> 520
+// 1x1 on 25,600 pixels: 106 us (131 TFLOP/s; the fp32 instruction's rate 70).
 //
 // Block: 256 threads, BM output channels x BN pixels, 2 x 2 waves of (BM / 2)
 // x (BN / 2), in 32 x 32 fragments.  K in chunks of NO octets (8 values): while
