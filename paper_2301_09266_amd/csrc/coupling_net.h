@@ -24,11 +24,11 @@
 // levels of a flow have few pixels (1,600 at 4 x 4, batch 100).
 //
 // What bounds it: a tile reads all weights from L2 (2.4 MB with its input at C =
-// 12, 98% of it hits: 71 GB/s a compute unit, 30 bytes a cycle, in each of the four
+// 12, 98% of it hits: 78 GB/s a compute unit, 32 bytes a cycle, in each of the four
 // rounds of 800 tiles on 256 compute units, the last of 32), with the matrix cores
-// at 41% of their rate meanwhile; the small levels have fewer tiles than the chip
+// at 45% of their rate meanwhile; the small levels have fewer tiles than the chip
 // compute units.  hid = 512, batch 100, against three fp32 GEMM launches:
-// 12 x 16 x 16 304 -> 133 us, 24 x 8 x 8 132 -> 43 us, 48 x 4 x 4 87 -> 49 us.
+// 12 x 16 x 16 304 -> 122 us, 24 x 8 x 8 132 -> 38 us, 48 x 4 x 4 87 -> 46 us.
 //
 // Sums that are not finite (infinite inputs, an overflow; the split parts of
 // infinities meet opposite infinities and zeros) are computed again with the
