@@ -75,6 +75,25 @@ static void plans() {
     EXPECT(finc_inverse_plan(7, 1, 1, 12, 16, 16, 3, nullptr, 1) == FINC_EINVAL);
 }
 
+// Images of up to 2^24 - 1 pixels in a few rows or columns: their layouts' sizes
+// pass 2^31.
+static void wide() {
+    const int N = (1 << 24) - 1;
+    const int HW[][2] = {{1, N}, {N, 1}, {2, N / 2}, {16, N / 16}, {N / 3, 3}, {1, 16519032}};
+    for (int kind = FINC_PLAN_LAYER; kind <= FINC_PLAN_SPLIT; ++kind)
+        for (int C = 1; C <= FINC_MAX_C; ++C)
+            for (int k = 1; k <= FINC_MAX_K; ++k)
+                for (const auto &hw : HW) {
+                    int info[6], fi[3];
+                    const int r = finc_inverse_plan(kind, 1, 1, C, hw[0], hw[1], k, info, 1);
+                    EXPECT(r == FINC_EINVAL || r == FINC_EUNSUPPORTED || (r == 1 && info[3] == 1));
+                    const int f = finc_forward_plan(kind, 1, C, hw[0], hw[1], k, 1, fi);
+                    EXPECT(f == FINC_EINVAL || f == FINC_EUNSUPPORTED || f == FINC_OK);
+                    EXPECT(f != FINC_OK || (hw[1] <= 3 && fi[2] <= 160 * 1024));
+                    (void)finc_backward_workspace_bytes(1, C, hw[0], hw[1], k);
+                }
+}
+
 static void sizes() {
     for (int C = -1; C <= FINC_MAX_C + 2; ++C)
         for (int k = -1; k <= FINC_MAX_K + 1; ++k) {
@@ -137,6 +156,7 @@ static void rejections() {
 
 int main() {
     plans();
+    wide();
     sizes();
     rejections();
     if (failures)
